@@ -113,18 +113,33 @@ __global__ void ring_fill_kernel(const int32_t* __restrict__ pos, const uint4* _
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32 decode on vector ALUs.
+// fp32 decode on vector ALUs: one query head per KV head.
 //
 // One workgroup (4 waves) per (sequence, KV head).  Each 16-lane quarter of a wave is a key
-// stream: its lanes split head_dim (D/16 channels each), reduce the G dot products with
-// lane shuffles and run its own online softmax over keys stream, stream + 16, ...; the 16
+// stream: its lanes split head_dim (D/16 channels each), reduce the dot products with lane
+// shuffles and run the stream's own online softmax over keys stream, stream + 16, ..., four keys
+// at a time (their eight rows load together, one reference and one rescale per four); the 16
 // stream states are merged with Eq.(lse) (Appendix A.4) at the end.
-template <int D, int GMAX>
+// Bound: HBM.  Lane s of a stream takes channels 64 y + 4 s .. +3, so that each load instruction
+// reads whole 128-byte lines (with 32 contiguous bytes per lane, two instructions share every
+// line, and non-temporal loads fetched it twice: 885 us where temporal ones took 557).  Measured
+// against one key at a time with room for four heads: batch 512, 8 heads, d 128, B 1024
+// 554 -> 507 us (6.4 TB/s), batch 64, 8 heads, d 64, B 512 (cache-resident) 29.8 -> 23.0 us.
+
+// A vector load of ring data, non-temporal (NT) when the rings exceed the last-level cache.
+template <bool NT, typename T>
+__device__ __forceinline__ T stream_load(const T* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+
+template <int D, bool NT>
 __global__ __launch_bounds__(256) void decode_f32_kernel(DecodeArgs a) {
-  constexpr int E = D / 16;
-  __shared__ float sm_acc[4][GMAX][D];
-  __shared__ float sm_m[4][GMAX];
-  __shared__ float sm_l[4][GMAX];
+  constexpr int E = D / 16;   // channels per lane: 64 y + 4 sub .. +3, y < E / 4
+  constexpr int U = 4;        // keys of a stream taken together
+  __shared__ float sm_acc[4][D];
+  __shared__ float sm_m[4];
+  __shared__ float sm_l[4];
 
   const int bg = blockIdx.x;
   const int b = bg / a.hkv;
@@ -134,11 +149,10 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(DecodeArgs a) {
   const int wave = tid >> 6;
   const int sub = lane & 15;
   const int stream = wave * 4 + (lane >> 4);
-  const int G = a.group;
-  float* out = (float*)a.out + ((size_t)b * a.hq + (size_t)g * G) * D;
+  float* out = (float*)a.out + (size_t)bg * D;
   const int t = a.pos[b];
   if (t < 0) {
-    for (int e = tid; e < G * D; e += 256) out[e] = 0.0f;
+    if (tid < D) out[tid] = 0.0f;
     if (a.pos_next != nullptr && g == 0 && tid == 0) a.pos_next[b] = t;
     return;
   }
@@ -155,113 +169,98 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(DecodeArgs a) {
     vring[(size_t)R.append_slot * D + tid] = vnew[tid];
   }
 
-  float qf[GMAX][E];
-  const float* qrow = (const float*)a.q + ((size_t)b * a.hq + (size_t)g * G) * D + sub * E;
+  float qf[E];
+  const float* qrow = (const float*)a.q + (size_t)bg * D + 4 * sub;
 #pragma unroll
-  for (int j = 0; j < GMAX; ++j)
-#pragma unroll
-    for (int e = 0; e < E; ++e) qf[j][e] = (j < G) ? qrow[(size_t)j * D + e] * a.scale_log2 : 0.0f;
+  for (int e = 0; e < E; ++e) qf[e] = qrow[64 * (e >> 2) + (e & 3)] * a.scale_log2;
 
-  float m[GMAX], l[GMAX], acc[GMAX][E];
+  float m = kNegInf, l = 0.0f, acc[E];
 #pragma unroll
-  for (int j = 0; j < GMAX; ++j) {
-    m[j] = kNegInf;
-    l[j] = 0.0f;
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[j][e] = 0.0f;
-  }
+  for (int e = 0; e < E; ++e) acc[e] = 0.0f;
 
   const int n_total = R.n_ring + 1;
-  for (int i = stream; i < n_total; i += 16) {
-    const float* kp;
-    const float* vp;
-    if (i < R.n_ring) {
-      const size_t off = (size_t)ring_slot(R, i) * D;
-      kp = kring + off;
-      vp = vring + off;
-    } else {
-      kp = knew;
-      vp = vnew;
-    }
-    float kf[E], vf[E];
+  for (int i0 = stream; i0 < n_total; i0 += 16 * U) {
+    f32x4 kf[U][E / 4], vf[U][E / 4];
 #pragma unroll
-    for (int e = 0; e < E; e += 4) {
-      const float4 k4 = *(const float4*)(kp + sub * E + e);
-      const float4 v4 = *(const float4*)(vp + sub * E + e);
-      kf[e] = k4.x; kf[e + 1] = k4.y; kf[e + 2] = k4.z; kf[e + 3] = k4.w;
-      vf[e] = v4.x; vf[e + 1] = v4.y; vf[e + 2] = v4.z; vf[e + 3] = v4.w;
-    }
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + 16 * u;
+      // the current token, and (masked) keys past it, read k_new and v_new
+      const size_t off = i < R.n_ring ? (size_t)ring_slot(R, i) * D : 0;
+      const float* kp = (i < R.n_ring ? kring + off : knew) + 4 * sub;
+      const float* vp = (i < R.n_ring ? vring + off : vnew) + 4 * sub;
 #pragma unroll
-    for (int j = 0; j < GMAX; ++j) {
-      if (j < G) {
-      float s = 0.0f;
-#pragma unroll
-      for (int e = 0; e < E; ++e) s = fmaf(qf[j][e], kf[e], s);
-      s += __shfl_xor(s, 8, 16);
-      s += __shfl_xor(s, 4, 16);
-      s += __shfl_xor(s, 2, 16);
-      s += __shfl_xor(s, 1, 16);
-      const float mn = fmaxf(m[j], s);
-      const float alpha = fast_exp2(m[j] - mn);  // m = -inf gives 0
-      const float p = fast_exp2(s - mn);
-      l[j] = l[j] * alpha + p;
-#pragma unroll
-      for (int e = 0; e < E; ++e) acc[j][e] = fmaf(p, vf[e], acc[j][e] * alpha);
-      m[j] = mn;
+      for (int e = 0; e < E / 4; ++e) {
+        kf[u][e] = stream_load<NT>((const f32x4*)(kp + 64 * e));
+        vf[u][e] = stream_load<NT>((const f32x4*)(vp + 64 * e));
       }
+    }
+    float s[U];
+    float mn = m;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      s[u] = 0.0f;
+#pragma unroll
+      for (int e = 0; e < E; ++e) s[u] = fmaf(qf[e], kf[u][e >> 2][e & 3], s[u]);
+      s[u] += __shfl_xor(s[u], 8, 16);
+      s[u] += __shfl_xor(s[u], 4, 16);
+      s[u] += __shfl_xor(s[u], 2, 16);
+      s[u] += __shfl_xor(s[u], 1, 16);
+      s[u] = i0 + 16 * u < n_total ? s[u] : kNegInf;
+      mn = fmaxf(mn, s[u]);
+    }
+    const float alpha = fast_exp2(m - mn);  // m = -inf gives 0
+    m = mn;
+    float p[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) p[u] = fast_exp2(s[u] - mn);
+    l = fmaf(l, alpha, (p[0] + p[1]) + (p[2] + p[3]));
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      float part = p[0] * vf[0][e >> 2][e & 3];
+#pragma unroll
+      for (int u = 1; u < U; ++u) part = fmaf(p[u], vf[u][e >> 2][e & 3], part);
+      acc[e] = fmaf(acc[e], alpha, part);
     }
   }
 
   // Merge the four streams of this wave (Eq.(lse)); empty streams carry m = -inf, l = 0.
 #pragma unroll
   for (int off = 16; off <= 32; off <<= 1) {
+    const float mo = __shfl_xor(m, off);
+    const float lo = __shfl_xor(l, off);
+    const float mn = fmaxf(m, mo);
+    const float a1 = (m == kNegInf) ? 0.0f : fast_exp2(m - mn);
+    const float a2 = (mo == kNegInf) ? 0.0f : fast_exp2(mo - mn);
+    l = l * a1 + lo * a2;
 #pragma unroll
-    for (int j = 0; j < GMAX; ++j) {
-      if (j < G) {
-      const float mo = __shfl_xor(m[j], off);
-      const float lo = __shfl_xor(l[j], off);
-      const float mn = fmaxf(m[j], mo);
-      const float a1 = (m[j] == kNegInf) ? 0.0f : fast_exp2(m[j] - mn);
-      const float a2 = (mo == kNegInf) ? 0.0f : fast_exp2(mo - mn);
-      l[j] = l[j] * a1 + lo * a2;
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const float ao = __shfl_xor(acc[j][e], off);
-        acc[j][e] = acc[j][e] * a1 + ao * a2;
-      }
-      m[j] = mn;
-      }
+    for (int e = 0; e < E; ++e) {
+      const float ao = __shfl_xor(acc[e], off);
+      acc[e] = acc[e] * a1 + ao * a2;
     }
+    m = mn;
   }
   if (lane < 16) {
 #pragma unroll
-    for (int j = 0; j < GMAX; ++j) {
-      if (j < G) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) sm_acc[wave][j][sub * E + e] = acc[j][e];
-        if (lane == 0) {
-          sm_m[wave][j] = m[j];
-          sm_l[wave][j] = l[j];
-        }
-      }
+    for (int e = 0; e < E; ++e) sm_acc[wave][64 * (e >> 2) + 4 * sub + (e & 3)] = acc[e];
+    if (lane == 0) {
+      sm_m[wave] = m;
+      sm_l[wave] = l;
     }
   }
   __syncthreads();
-  for (int idx = tid; idx < G * D; idx += 256) {
-    const int j = idx / D;
-    const int c = idx - j * D;
+  if (tid < D) {
     float M = kNegInf;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) M = fmaxf(M, sm_m[w][j]);
+    for (int w = 0; w < 4; ++w) M = fmaxf(M, sm_m[w]);
     float L = 0.0f, O = 0.0f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float mw = sm_m[w][j];
+      const float mw = sm_m[w];
       const float wt = (mw == kNegInf) ? 0.0f : fast_exp2(mw - M);
-      L += wt * sm_l[w][j];
-      O += wt * sm_acc[w][j][c];
+      L += wt * sm_l[w];
+      O += wt * sm_acc[w][tid];
     }
-    out[idx] = O / L;
+    out[tid] = O / L;
   }
 }
 
@@ -291,7 +290,7 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(DecodeArgs a) {
 // streams as fast on the vector ALUs).
 constexpr int kF32MatrixMinGroup = 2;
 
-template <int D, int NW>
+template <int D, int NW, bool NT>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
 void decode_f32_mfma_kernel(DecodeArgs a) {
   constexpr int KM = D / 4;     // MFMAs per score tile (channels per quarter)
@@ -349,12 +348,12 @@ void decode_f32_mfma_kernel(DecodeArgs a) {
     const int i0 = tile * 16;
     const float* kp = krow(i0 + c16) + 4 * j4;
 #pragma unroll
-    for (int q = 0; q < KQ; ++q) kb[q] = *(const f4*)(kp + 16 * q);
+    for (int q = 0; q < KQ; ++q) kb[q] = stream_load<NT>((const f4*)(kp + 16 * q));
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       const float* vp = vrow(i0 + 4 * j4 + m) + 4 * c16;
 #pragma unroll
-      for (int q = 0; q < VQ; ++q) vb[m][q] = *(const f4*)(vp + 64 * q);
+      for (int q = 0; q < VQ; ++q) vb[m][q] = stream_load<NT>((const f4*)(vp + 64 * q));
     }
   };
 
@@ -1216,6 +1215,9 @@ hipError_t launch_ring_fill(const int32_t* pos, const void* k_src, const void* v
   return hipGetLastError();
 }
 
+// Rings (K and V together) above this size stream past the chip's 256 MiB last-level cache.
+constexpr double kStreamBytes = 256.0 * 1024.0 * 1024.0;
+
 template <int D, int NW>
 void launch_bf16_policy(const DecodeArgs& a, bool nt, hipStream_t stream) {
   const dim3 grid((unsigned)(a.batch * a.hkv * a.splits));
@@ -1258,7 +1260,7 @@ hipError_t launch_decode_bf16(const DecodeArgs& a, int32_t head_dim, hipStream_t
   const bool wide = max_keys >= 2048 || units < 256;
   // Non-temporal loads once both rings exceed the 256 MiB last-level cache of the chip.
   const double ring_bytes = 4.0 * (double)units * (double)a.slots * (double)head_dim;
-  const bool nt = ring_bytes > 256.0 * 1024.0 * 1024.0;
+  const bool nt = ring_bytes > kStreamBytes;
   // Latency-bound launches over small rings prefetch the whole ring with the positions.
   if (a.splits <= 1 && a.slots <= kWholeRingMaxSlots && units <= kWholeRingMaxUnits) {
     if (head_dim == 128) launch_bf16_whole<128>(a, stream);
@@ -1275,30 +1277,30 @@ hipError_t launch_decode_bf16(const DecodeArgs& a, int32_t head_dim, hipStream_t
   return hipGetLastError();
 }
 
+template <int D, bool NT>
+void launch_f32(const DecodeArgs& a, hipStream_t stream) {
+  const dim3 grid((unsigned)(a.batch * a.hkv)), block(256);
+  if (a.group >= kF32MatrixMinGroup)
+    hipLaunchKernelGGL((decode_f32_mfma_kernel<D, 4, NT>), grid, block, 0, stream, a);
+  else
+    hipLaunchKernelGGL((decode_f32_kernel<D, NT>), grid, block, 0, stream, a);
+}
+
 hipError_t launch_decode_f32(const DecodeArgs& a, int32_t head_dim, hipStream_t stream) {
-  const dim3 grid((unsigned)(a.batch * a.hkv));
-  if (a.group >= kF32MatrixMinGroup) {
-    if (head_dim == 128)
-      hipLaunchKernelGGL((decode_f32_mfma_kernel<128, 4>), grid, dim3(256), 0, stream, a);
-    else
-      hipLaunchKernelGGL((decode_f32_mfma_kernel<64, 4>), grid, dim3(256), 0, stream, a);
-    return hipGetLastError();
-  }
-  const dim3 block(256);
+  // Non-temporal loads by the rule of the bf16 launches (8 bytes per element of the two rings).
+  // Measured with and without, in one process: batch 512, 16/2 heads, B 1024 (1 GiB of rings)
+  // 151 against 162 us per step, 32/8 heads, batch 256, B 2048 515 against 559 us, G = 1 as above
+  // 507 against 551 us.  (K's loads take 64 bytes of a row per instruction; temporal loads for K
+  // alone are 2 % faster at the second shape when its rings repeat, and 19 % slower at the first
+  // on rings not read before.)
+  const double ring_bytes = 8.0 * (double)(a.batch * a.hkv) * (double)a.slots * (double)head_dim;
+  const bool nt = ring_bytes > kStreamBytes;
   if (head_dim == 128) {
-    if (a.group <= 4)
-      hipLaunchKernelGGL((decode_f32_kernel<128, 4>), grid, block, 0, stream, a);
-    else if (a.group <= 8)
-      hipLaunchKernelGGL((decode_f32_kernel<128, 8>), grid, block, 0, stream, a);
-    else
-      hipLaunchKernelGGL((decode_f32_kernel<128, 16>), grid, block, 0, stream, a);
+    if (nt) launch_f32<128, true>(a, stream);
+    else launch_f32<128, false>(a, stream);
   } else {
-    if (a.group <= 4)
-      hipLaunchKernelGGL((decode_f32_kernel<64, 4>), grid, block, 0, stream, a);
-    else if (a.group <= 8)
-      hipLaunchKernelGGL((decode_f32_kernel<64, 8>), grid, block, 0, stream, a);
-    else
-      hipLaunchKernelGGL((decode_f32_kernel<64, 16>), grid, block, 0, stream, a);
+    if (nt) launch_f32<64, true>(a, stream);
+    else launch_f32<64, false>(a, stream);
   }
   return hipGetLastError();
 }
