@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "pbb_index.h"
+
 namespace pbb {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -54,6 +56,19 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// Waits until at most `ahead` groups (wave-uniform, at most N) of OPS vector-memory instructions
+// each, the youngest ones, are outstanding.
+template <int N, int OPS>
+__device__ __forceinline__ void wait_groups(int ahead) {
+  static_assert(N * OPS < 64, "vmcnt immediate");
+  if constexpr (N == 0) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+  } else {
+    if (ahead >= N) __builtin_amdgcn_s_waitcnt(0x0F70 | ((N * OPS) & 15) | (((N * OPS) >> 4) << 14));
+    else wait_groups<N - 1, OPS>(ahead);
+  }
+}
+
 // First source a(t) of the support of target t: PBB (mode 0) max(0, h(floor(t/h) - 1)) with
 // h = block/2 (Sec. 3 "Flash-PBB"), SWA max(0, t - window + 1) (Prop. 2).  Never decreases in t.
 __device__ __forceinline__ int support_start(int mode, int block, int window, int t) {
@@ -93,6 +108,38 @@ __device__ __forceinline__ float sum_xor16_32(float x) {
   auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
+
+// Two floats as a bf16 pair (x in the low half), round to nearest even: one instruction.
+__device__ __forceinline__ uint32_t pack_bf16(float x, float y) {
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+  const bf16x2 v = {(__bf16)x, (__bf16)y};
+  return __builtin_bit_cast(uint32_t, v);
+}
+
+// Two 16-channel output blocks of a 16-column tile (lane (c16, j4) holds channels 4 j4 .. +3 of
+// column c16 in each), scaled and packed to bf16: the odd quarters of the first swap with the even
+// quarters of the second, after which quarter j4 holds channels 8 (j4 / 2) .. +7 of block j4 mod 2.
+__device__ __forceinline__ u32x4 pair_blocks(f32x4 x, f32x4 y, float scale) {
+  const uint32_t x0 = pack_bf16(x[0] * scale, x[1] * scale), x1 = pack_bf16(x[2] * scale, x[3] * scale);
+  const uint32_t y0 = pack_bf16(y[0] * scale, y[1] * scale), y1 = pack_bf16(y[2] * scale, y[3] * scale);
+  const auto s0 = __builtin_amdgcn_permlane16_swap(x0, y0, false, false);
+  const auto s1 = __builtin_amdgcn_permlane16_swap(x1, y1, false, false);
+  return u32x4{(uint32_t)s0[0], (uint32_t)s1[0], (uint32_t)s0[1], (uint32_t)s1[1]};
+}
+
+// LDS tiles of the prefill and backward kernels.  A 32-row tile (rows of D bf16) is stored as
+// [row / 8][128-byte line of the row][8 rows x 8 pieces of 16 bytes], one 1 KiB LDS DMA per block,
+// which reads whole cache lines; tile_block is the byte offset of row group y and line z.  Piece p
+// of a line of row r sits at slot 8 (r mod 8) + (p ^ tile_swz(r)).  Both reads of a tile are then
+// free of bank conflicts (64 banks; a 16-byte read serves per cycle the 16 lanes that share lane
+// bit 5 and the parity of lane bits 2..4, an 8-byte or transposed read the 32 lanes that share the
+// parity of lane bits 3..5), and a read's address is a lane constant for its piece within the line
+// (2 for row operands, 4 for transposed reads) plus an immediate.
+template <int D>
+__device__ __forceinline__ constexpr int tile_block(int y, int z) {
+  return (y * (D / 64) + z) * 1024;
+}
+__device__ __forceinline__ constexpr int tile_swz(int r) { return r & 6; }
 
 // One 16-byte LDS DMA (global_load_lds) from a wave-uniform base plus a 32-bit lane offset, so
 // that the address is formed by the instruction (scalar base + vector offset) rather than by

@@ -8,20 +8,30 @@
 // sliding-window variant uses [max(0, t-W+1), t] (Prop. 2).  a(t) never decreases, so the
 // keys any run of consecutive positions needs form one interval.
 //
-// Work unit: TQ = floor(16*QC*NW / G) consecutive positions of one (sequence, KV head) with
-// all G query heads of that KV head, i.e. 16*QC*NW query columns ordered position-major,
-// head-minor (native grouped-query attention: the K/V tile is read once for the group).
-// Keys of the unit's interval stream through LDS in 32-key steps, three stages deep, each
-// tile loaded once per workgroup by LDS DMA and shared by the 4 waves; each wave owns QC
-// groups of 16 columns.  Per step a wave computes S^T = K Q^T and O^T += V^T P^T on
-// v_mfma_f32_16x16x32_bf16 exactly as the decode kernel does, the 16 B-operand columns being
-// 16 queries; per-column bounds mask the tile; the online softmax keeps fp32 running
-// maxima and sums (the log-sum-exp rescaling of Appendix A.4, Eq.(lse)).  Outputs are rounded
-// to bf16 (RNE); the log-partition is written in natural-log units.  Finally every workgroup
-// copies those of its positions that fall in the last `slots` positions of the prompt into the
-// ring (slot s mod slots, Appendix F.1), the state decode continues from.
-
-#include <type_traits>
+// Work unit: TQ = floor(128 / G) consecutive positions of one (sequence, KV head) with all G
+// query heads of that KV head, i.e. up to 128 query columns ordered position-major, head-minor
+// (native grouped-query attention: the K/V tile is read once for the group), 32 columns per wave
+// in two groups of 16.  Keys of the unit's interval stream through LDS in 32-key steps, each tile
+// loaded once per workgroup by LDS DMA and shared by the 4 waves.  Per step a wave computes
+// S^T = K Q^T and O^T += V^T P^T on v_mfma_f32_16x16x32_bf16 exactly as the decode kernel does,
+// the 16 B-operand columns being 16 queries; per-column bounds mask the tile, and a wave computes
+// only the steps that its own columns need.  The online softmax keeps fp32 running references and
+// sums (the log-sum-exp rescaling of Appendix A.4, Eq.(lse)).  Outputs are rounded to bf16 (RNE);
+// the log-partition is written in natural-log units.  Finally every workgroup copies those of its
+// positions that fall in the last `slots` positions of the prompt into the ring (slot s mod slots,
+// Appendix F.1), the state decode continues from.
+//
+// LDS tiles: tile_block() and tile_swz() in pbb_device.h.
+//
+// Bound: instruction issue (matrix and vector work of a SIMD overlap only in part; at c3's heads
+// the matrix cores draw the card's power limit as well).  What a tile costs beside its key steps
+// counts at d = 64 and small blocks, where it walks 3 to 5 of them: index arithmetic by FastDiv
+// instead of divisions, packed conversions and 16-byte stores in the epilogue, steps skipped per
+// wave, and LDS addresses that are two or four lane constants plus immediates took the paper's
+// shape (12/2 heads, d 64, B 128, n 65536; 238 MB) from 74.1 to 61.4 us (3.9 TB/s) and c3's heads
+// (n 16384, batch 4) from 1533 to 1491 us (1060 TFLOP/s).  32x32x16 matrix instructions in the
+// same structure (32 columns at once, a fifth fewer vector instructions) measured 1574 us there
+// and 62.0 at the paper's shape.
 
 #include "pbb_device.h"
 #include "pbb_internal.h"
@@ -29,41 +39,60 @@
 namespace pbb {
 namespace {
 
-// Waves per workgroup, 16-column groups per wave and LDS stages (d = 128, d = 64).
-constexpr int kPrefillWaves128 = 4;
-constexpr int kPrefillWaves64 = 4;
-constexpr int kPrefillStages128 = 3;
-constexpr int kPrefillStages64 = 5;  // a tile at d = 64 walks few key steps: all in flight early
-constexpr int kPrefillColGroups128 = 2;
-constexpr int kPrefillColGroups64 = 2;
-
+// Waves per workgroup and 16-column groups per wave.  Measured with the present kernel: one group
+// per wave 1.4x slower at c3's heads, n 8192 (twice the LDS bytes per product); 8 waves of two
+// groups 11 % slower there and 2 % at the paper's shape (every barrier holds twice the waves).
+constexpr int kPrefillWaves = 4;
+constexpr int kPrefillGroups = 2;
+constexpr int kPrefillCols = 16 * kPrefillGroups * kPrefillWaves;
+// LDS stages and the occupancy the register budget is set for (waves per SIMD = workgroups per
+// CU): three at d = 128 (166 VGPRs, 48 KiB of LDS), four at d = 64 (106 VGPRs, 32 KiB).  Deeper
+// pipelines cost occupancy: five and eight stages are 20 to 60 % slower, at one workgroup per CU
+// too.
+constexpr int kPrefillStages128 = 3, kPrefillOcc128 = 3;
+constexpr int kPrefillStages64 = 4, kPrefillOcc64 = 4;
 // Starting reference of the running maximum (log2 units): finite and below any score.
 constexpr float kNoScore = -1.0e30f;
 
-__device__ __forceinline__ int support_lo(const PrefillArgs& a, int t) {
-  return support_start(a.mode, a.block, a.window, t);
-}
+// Launches of at most kByWeightMaxBlocks workgroups (16 per CU), with at least kByWeightMinPhases
+// tiles per half-block (SWA: per prompt), deal out their tiles heaviest first instead of in order.
+// In order, a CU's few workgroups often have the same phase (with 32 tiles per unit, the 32 CUs of
+// an XCD each take one tile index of every unit) and the launch waits for the CUs with the longest
+// intervals; with many workgroups per CU that evens out, and tiles in order share their keys in
+// an XCD's L2.  Measured, by weight against in order, 32/8 heads, d 128, B 2048: batch 3, n 1021
+// (768 workgroups) 36.1 against 49.1 us; batch 1, n 2000 54.8 / 58.7; batch 4, n 2048 146 / 165;
+// batch 4, n 4096 (4096) 341 / 347; batch 4, n 8192 (8192) 839 / 721.  16/4 heads, d 64, B 512 (8
+// tiles per half-block): batch 8, n 500 15.1 / 17.5, batch 4, n 8192 (4096) 81.9 / 81.5.  12/2
+// heads, d 64, B 128 (3 tiles per half-block, which mix anyway): n 16384 20.8 / 18.7.
+constexpr int kByWeightMaxBlocks = 4096;
+constexpr int kByWeightMinPhases = 8;
 
-// Three waves per SIMD (three workgroups of 48 KiB LDS per CU): the register budget this sets
-// at d = 128 (168) leaves a few values of the epilogue in scratch, outside the key loop.
-template <int D, int QC, int NW, int ST>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3)))
-void prefill_bf16_kernel(PrefillArgs a, int tq, int tiles) {
+// Launch constants: positions per tile, tiles per unit and the divisors of the index arithmetic.
+struct PrefillPlan {
+  int tq;
+  int tiles;
+  int by_weight;   // 1: tiles are dealt out by weight (order)
+  FastDiv by_tiles, by_hkv, by_group, by_half;
+  TileOrder order;
+};
+
+template <int D, int ST, int OCC>
+__global__ __launch_bounds__(kPrefillWaves * 64) __attribute__((amdgpu_waves_per_eu(OCC)))
+void prefill_bf16_kernel(PrefillArgs a, PrefillPlan pl) {
+  constexpr int NW = kPrefillWaves;
+  constexpr int QC = kPrefillGroups;
   constexpr int KK = D / 32;            // 32-channel slices of the score contraction
   constexpr int NB = D / 16;            // 16-channel blocks of the output
   constexpr int ROWB = D * 2;           // bytes of one K or V row
   constexpr int PPR = D / 8;            // 16-byte pieces per row
-  constexpr int RPI = 64 / PPR;         // rows per 1 KiB DMA group
-  constexpr int NG = 32 / RPI;          // DMA groups per step and tensor
-  constexpr int KTILE = 32 * ROWB;
-  constexpr int VTILE = 32 * ROWB;
-  constexpr int BUF = KTILE + VTILE;
+  constexpr int LN = D / 64;            // 128-byte lines per row
+  constexpr int HALF = 16 * ROWB;       // 16 rows of a tile
+  constexpr int TILE = 2 * HALF;
+  constexpr int BUF = 2 * TILE;         // K tile, then V tile
   constexpr int STAGES = ST;
-  static_assert(STAGES >= 3 && STAGES <= 5, "stages");
-  constexpr int OPS = 2 * NG;           // DMA instructions per step (K tile, then V tile)
-  constexpr int MYOPS = OPS / NW;       // issued by each wave
-  static_assert(OPS % NW == 0, "DMA split");
-  __shared__ __align__(256) unsigned char smem[STAGES * BUF];
+  static_assert(STAGES >= 3, "stages");
+  constexpr int WROWS = 64 / NW;        // rows of one tensor that a wave loads per step
+  __shared__ __align__(1024) unsigned char smem[STAGES * BUF];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -73,103 +102,121 @@ void prefill_bf16_kernel(PrefillArgs a, int tq, int tiles) {
   const int G = a.group;
   const int n = a.n;
 
-  // Workgroup i runs on XCD i mod 8; give each XCD a contiguous run of tiles so that tiles
-  // sharing keys (neighbours of one sequence and KV head) share that XCD's L2.
+  // First source of the support of target t.
+  auto support_lo = [&](int t) -> int {
+    const int lo = a.mode == kSupportPBB ? (a.block >> 1) * (pl.by_half.div(t) - 1)
+                                         : t - a.window + 1;
+    return max(lo, 0);
+  };
+
+  // Workgroup i runs on XCD i mod 8.
   const int nblk = gridDim.x;
-  const int per = nblk >> 3, rem = nblk & 7;
-  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-  const int tile_id = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + local;
-  const int bg = tile_id / tiles;
-  const int tile = tile_id - bg * tiles;
-  const int b = bg / a.hkv;
+  int bg, tile;
+  if (pl.by_weight) {
+    const int rank = pl.order.by_units.div(blockIdx.x);
+    bg = blockIdx.x - rank * (int)pl.order.by_units.d;
+    tile = pl.order.tile(rank);
+  } else {
+    // Give each XCD a contiguous run of tiles so that tiles sharing keys (neighbours of one
+    // sequence and KV head) share that XCD's L2.
+    const int per = nblk >> 3, rem = nblk & 7;
+    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+    const int tile_id =
+        (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + local;
+    bg = pl.by_tiles.div(tile_id);
+    tile = tile_id - bg * pl.tiles;
+  }
+  const int b = pl.by_hkv.div(bg);
   const int g = bg - b * a.hkv;
-  const int t0 = tile * tq;
-  const int t_last = min(n - 1, t0 + tq - 1);
-  const int kbeg = support_lo(a, t0);
-  const int s_first = kbeg >> 5;
+  const int t0 = tile * pl.tq;
+  const int t_last = min(n - 1, t0 + pl.tq - 1);
+  const int s_first = support_lo(t0) >> 5;
   const int nsteps = (t_last >> 5) - s_first + 1;
-  // Keys [mask_lo, mask_hi] are in the support of every position of the tile (a(t) never
-  // decreases): steps inside that range need no masking.
-  const int mask_lo = support_lo(a, t_last);
-  const int mask_hi = t0;
 
   const uint32_t rowstride = (uint32_t)a.hkv * ROWB;  // bytes between consecutive positions
   const unsigned char* kbase = (const unsigned char*)a.k + ((size_t)b * n * a.hkv + g) * ROWB;
   const unsigned char* vbase = (const unsigned char*)a.v + ((size_t)b * n * a.hkv + g) * ROWB;
 
-  // This lane's query columns: column c -> position t0 + c / G, head g*G + c % G.
-  int lo_c[QC], hi_c[QC], tcol[QC], hcol[QC];
-  bool valid[QC];
+  // This lane's query columns: column col -> position t0 + col / G, head g*G + col % G.  Columns
+  // past the tile's positions repeat its last position and are never stored.
+  const size_t row0 = ((size_t)b * n + t0) * a.hq + (size_t)g * G;   // row of (t0, head g*G)
+  struct Column {
+    int cp, head;   // position within the tile (the last one for columns past it), query head
+    bool valid;
+  };
+  auto column = [&](int qc, int c) -> Column {
+    const int col = (wave * QC + qc) * 16 + c;
+    const int cp = pl.by_group.div(col);
+    const int cu = min(cp, t_last - t0);
+    return Column{cu, col - cp * G, cp == cu};
+  };
+  auto row_offset = [&](const Column& x) { return (uint32_t)(x.cp * a.hq + x.head) * (uint32_t)ROWB; };
+  int tcol[QC], lo_c[QC];
   bf16x8 qB[QC][KK];
 #pragma unroll
   for (int qc = 0; qc < QC; ++qc) {
-    const int col = (wave * QC + qc) * 16 + c16;
-    const int cp = col / G;
-    tcol[qc] = t0 + cp;
-    hcol[qc] = g * G + (col - cp * G);
-    valid[qc] = cp < tq && tcol[qc] < n;
-    lo_c[qc] = valid[qc] ? support_lo(a, tcol[qc]) : 0x7fffffff;
-    hi_c[qc] = valid[qc] ? tcol[qc] : -1;
-    const uint16_t* qrow = (const uint16_t*)a.q +
-        ((size_t)(b * (size_t)n + (valid[qc] ? tcol[qc] : t0)) * a.hq + hcol[qc]) * D;
+    const Column x = column(qc, c16);
+    tcol[qc] = t0 + x.cp;
+    lo_c[qc] = support_lo(tcol[qc]);
+    const uint32_t off = row_offset(x) + 16 * j4;
+    const unsigned char* qbase = (const unsigned char*)a.q + row0 * ROWB;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      const u32x4 w = *(const u32x4*)(qrow + 32 * kk + 8 * j4);
-      const u32x4 zero = {0u, 0u, 0u, 0u};
-      qB[qc][kk] = __builtin_bit_cast(bf16x8, valid[qc] ? w : zero);
-    }
+    for (int kk = 0; kk < KK; ++kk) qB[qc][kk] = *(const bf16x8*)(qbase + (off + 64u * kk));
   }
 
-  auto swz_k = [](int r) -> int { return D == 128 ? (r & 15) : ((r >> 1) & 7); };
-  // V rows: 16-byte piece p of row r at p ^ swz_v(r).  The transposed reads below (4 rows x
-  // 8 bytes per 16 lanes) then hit distinct banks within every group of 32 lanes that an 8-byte
-  // LDS read serves per cycle on gfx950 (the lanes sharing the parity of lane bits 3..5).
-  auto swz_v = [](int r) -> int { return D == 128 ? 2 * (r & 7) : 2 * ((r >> 1) & 3); };
-  // LDS byte addresses of this lane's reads in stage 0: K rows c16 (and 16 + c16, a fixed
-  // distance on) at piece 4kk + j4, and the transposed V reads of chunk nb: row 4j4 + c16/4,
-  // channels 16nb + 4(c16 mod 4) .. +3 (rows 16.. a fixed distance on).  For d = 128, chunk
-  // nb + 4 sits at the byte offset of chunk nb with bit 7 flipped (rows are 256-byte aligned).
-  uint32_t kaddr[KK], vaddr[4];
+  // DMA of a step: each wave loads WROWS rows of K (the first half of the waves) or V, 128 bytes
+  // of 8 rows per instruction: lane l takes row l / 8 and the piece that belongs at slot l, addressed as a
+  // wave-uniform base plus a 32-bit lane offset.  In the last step, rows past t_last read row
+  // t_last instead (inside the tensor; masked for every column).
+  const unsigned char* const wsrc = wave >= NW / 2 ? vbase : kbase;
+  const int wrow = WROWS * (wave % (NW / 2));
+  const uint32_t doff = (uint32_t)(lane >> 3) * rowstride +
+                        (uint32_t)(((lane & 7) ^ tile_swz(lane >> 3)) << 4);
+  auto issue = [&](int stage, int st) {
+    unsigned char* dst = smem + stage * BUF + wave * WROWS * ROWB;
+#pragma unroll
+    for (int y = 0; y < WROWS / 8; ++y) {
+      const int r0 = min((s_first + st) * 32 + wrow + 8 * y, t_last);
+      const unsigned char* src = wsrc + (size_t)r0 * rowstride;
+      const uint32_t off = min(doff, (uint32_t)min(t_last - r0, 7) * rowstride + 112u);
+#pragma unroll
+      for (int z = 0; z < LN; ++z) dma16(src + 128 * z, off, dst + tile_block<D>(y, z));
+    }
+  };
+
+  // Steps 0 .. STAGES-2 go out first; step st then issues step st + STAGES - 1.
+#pragma unroll
+  for (int s = 0; s < STAGES - 1; ++s)
+    if (s < nsteps) issue(s, s);
+
+  // LDS byte addresses of this lane's reads in stage 0.  Row operand of slice kk: row c16, piece
+  // 4kk + j4: ra[kk mod 2] + 1024 (kk / 2); rows 16.. HALF further on.  Transposed reads of the
+  // values of chunk nb: row 4j4 + c16/4, channels 16nb + 4(c16 mod 4) .. +3:
+  // va[nb mod 4] + 1024 (nb / 4); rows 16.. HALF further on.
+  uint32_t ra[2], va[4];
   {
     const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk)
-      kaddr[kk] = base + c16 * ROWB + (((4 * kk + j4) ^ swz_k(c16)) << 4);
-    const int vrow = 4 * j4 + (c16 >> 2);
+    for (int x = 0; x < 2; ++x)
+      ra[x] = base + tile_block<D>(c16 >> 3, 0) + (c16 & 7) * 128 +
+              (((4 * x + j4) ^ tile_swz(c16)) << 4);
+    const int vr = 4 * j4 + (c16 >> 2);
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      vaddr[q] = base + KTILE + vrow * ROWB +
-                 (((2 * q + ((c16 & 3) >> 1)) ^ swz_v(vrow)) << 4) + ((c16 & 1) << 3);
+    for (int x = 0; x < 4; ++x)
+      va[x] = base + TILE + tile_block<D>(vr >> 3, 0) + (vr & 7) * 128 +
+              (((2 * x + ((c16 & 3) >> 1)) ^ tile_swz(vr)) << 4) + ((c16 & 1) << 3);
   }
   const __attribute__((address_space(3))) unsigned char* lds0 = nullptr;
 
-  // This wave's share of the DMA of a step: MYOPS 1 KiB pieces, each lane one 16-byte piece of
-  // one key row, addressed as a wave-uniform base (the step's first key row) plus a 32-bit lane
-  // offset.  In the last step, rows past t_last read the last piece of row t_last instead
-  // (inside the tensor; masked for every column).
-  uint32_t doff[MYOPS];
-#pragma unroll
-  for (int o = 0; o < MYOPS; ++o) {
-    const int op = wave * MYOPS + o;
-    const bool isv = op >= NG;
-    const int x = isv ? op - NG : op;
-    const int row = x * RPI + lane / PPR;
-    const int piece = (lane % PPR) ^ (isv ? swz_v(row) : swz_k(row));
-    doff[o] = (uint32_t)row * rowstride + (uint32_t)(piece * 16);
-  }
-  auto issue = [&](int stage, int st) {
-    unsigned char* tile_p = smem + stage * BUF;
-    const int k0 = (s_first + st) * 32;
-    const uint32_t lim = (uint32_t)min(t_last - k0, 31) * rowstride + (ROWB - 16);
-#pragma unroll
-    for (int o = 0; o < MYOPS; ++o) {
-      const int op = wave * MYOPS + o;
-      const bool isv = op >= NG;
-      const int x = isv ? op - NG : op;
-      dma16((isv ? vbase : kbase) + (size_t)k0 * rowstride, min(doff[o], lim),
-            tile_p + (isv ? KTILE : 0) + x * 1024);
-    }
-  };
+  // The wave's own range of steps [wlo, whi] (its columns' positions tw_lo .. tw_hi), and the
+  // run [ua, ub) of them whose keys all lie in every column's support (a(t) never decreases).
+  const int tw_lo = t0 + pl.by_group.div(wave * 16 * QC);
+  const int tw_hi = min(t0 + pl.by_group.div(wave * 16 * QC + 16 * QC - 1), t_last);
+  const int a_hi = support_lo(tw_hi);
+  const int wlo = tw_lo <= t_last ? (support_lo(tw_lo) >> 5) - s_first : nsteps;
+  const int whi = (tw_hi >> 5) - s_first;
+  const int ua = ((a_hi + 31) >> 5) - s_first;
+  const int ub = ((tw_lo + 1) >> 5) - s_first;
 
   // m starts at a finite floor below any score, so that a column whose keys are all masked so
   // far gets exp2(-inf - m) = 0 without a separate test; its first real maximum always moves m.
@@ -182,32 +229,29 @@ void prefill_bf16_kernel(PrefillArgs a, int tq, int tiles) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[qc][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   }
-
-  // Steps 0 .. STAGES-2 go out first; step st then issues step st + STAGES - 1.
+  const float sc = a.scale_log2;
+  // the queries have landed (the key steps issued after them may still be in flight)
 #pragma unroll
-  for (int s = 0; s < STAGES - 1; ++s)
-    if (s < nsteps) issue(s, s);
-  int rstage = 0;
-  constexpr int W1 = 0x0F70 | (MYOPS & 15) | ((MYOPS >> 4) << 14);
-  constexpr int W2 = 0x0F70 | ((2 * MYOPS) & 15) | (((2 * MYOPS) >> 4) << 14);
-  constexpr int W3 = 0x0F70 | ((3 * MYOPS) & 15) | (((3 * MYOPS) >> 4) << 14);
+  for (int qc = 0; qc < QC; ++qc)
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(qB[qc][kk]));
 
-  auto step = [&](int st, auto masked) {
+  int rstage = 0;
+  constexpr int OPS = WROWS / 8 * LN;           // DMA instructions of a wave per step
+
+  for (int st = 0; st < nsteps; ++st) {
     // This wave's loads of step st have landed once at most the loads of the steps issued
     // after it (up to STAGES - 2) are outstanding; the barrier then covers every wave's loads,
     // and every wave is done with step st-1, whose stage the loads of step st+STAGES-1 reuse.
-    const int ahead = min(STAGES - 2, nsteps - 1 - st);
-    if (ahead >= 3) __builtin_amdgcn_s_waitcnt(W3);
-    else if (ahead == 2) __builtin_amdgcn_s_waitcnt(W2);
-    else if (ahead == 1) __builtin_amdgcn_s_waitcnt(W1);
-    else __builtin_amdgcn_s_waitcnt(0x0F70);
+    wait_groups<STAGES - 2, OPS>(min(STAGES - 2, nsteps - 1 - st));
     lds_barrier();
     if (st + STAGES - 1 < nsteps)
       issue(rstage == 0 ? STAGES - 1 : rstage - 1, st + STAGES - 1);
     __builtin_amdgcn_sched_barrier(0);
-
     const uint32_t sb = (uint32_t)(rstage * BUF);
-    const int k0 = (s_first + st) * 32;
+    rstage = rstage == STAGES - 1 ? 0 : rstage + 1;
+    if (st < wlo || st > whi) continue;
+
     f32x4 s0[QC], s1[QC];
 #pragma unroll
     for (int qc = 0; qc < QC; ++qc) {
@@ -216,13 +260,26 @@ void prefill_bf16_kernel(PrefillArgs a, int tq, int tiles) {
     }
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      const auto* kp = lds0 + kaddr[kk] + sb;
+      const auto* kp = lds0 + ra[kk & 1] + sb + 1024 * (kk >> 1);
       const bf16x8 ka = *(const __attribute__((address_space(3))) bf16x8*)(kp);
-      const bf16x8 kb = *(const __attribute__((address_space(3))) bf16x8*)(kp + 16 * ROWB);
+      const bf16x8 kb = *(const __attribute__((address_space(3))) bf16x8*)(kp + HALF);
 #pragma unroll
       for (int qc = 0; qc < QC; ++qc) {
         s0[qc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qB[qc][kk], s0[qc], 0, 0, 0);
         s1[qc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb, qB[qc][kk], s1[qc], 0, 0, 0);
+      }
+    }
+    // Element e of s0 is key k0 + 4 j4 + e of the lane's column, of s1 key k0 + 16 + 4 j4 + e.
+    if (st < ua || st >= ub) {
+      const int k0 = (s_first + st) * 32 + 4 * j4;
+#pragma unroll
+      for (int qc = 0; qc < QC; ++qc) {
+        const int lo = lo_c[qc] - k0, up = tcol[qc] - k0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s0[qc][e] = e >= lo && e <= up ? s0[qc][e] : kNegInf;
+          s1[qc][e] = 16 + e >= lo && 16 + e <= up ? s1[qc][e] : kNegInf;
+        }
       }
     }
     // Online softmax in log2 units with a lazily moved reference m (the log-sum-exp rescaling
@@ -233,20 +290,8 @@ void prefill_bf16_kernel(PrefillArgs a, int tq, int tiles) {
     // more than 8 log2 units above m, and steps where several rise more than 5.  No other step
     // computes a maximum.  The result is the same softmax (numerator and denominator share
     // every reference change), and the weights that enter the sums and products stay <= 2^8.
-    const float c = a.scale_log2;
     bf16x8 pB[QC];
     float ps[QC];
-    if constexpr (decltype(masked)::value) {
-#pragma unroll
-      for (int qc = 0; qc < QC; ++qc)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int key = k0 + (e < 4 ? 4 * j4 + e : 16 + 4 * j4 + (e - 4));
-          const bool in = key >= lo_c[qc] && key <= hi_c[qc];
-          if (e < 4) s0[qc][e] = in ? s0[qc][e] : kNegInf;
-          else s1[qc][e - 4] = in ? s1[qc][e - 4] : kNegInf;
-        }
-    }
     auto weights = [&]() {
       bool over = false;
 #pragma unroll
@@ -254,8 +299,8 @@ void prefill_bf16_kernel(PrefillArgs a, int tq, int tiles) {
         float sum = 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float sc = e < 4 ? s0[qc][e] : s1[qc][e - 4];
-          const float pe = fast_exp2(__builtin_fmaf(sc, c, -m[qc]));
+          const float pe =
+              fast_exp2(__builtin_fmaf(e < 4 ? s0[qc][e] : s1[qc][e - 4], sc, -m[qc]));
           sum += pe;
           pB[qc][e] = (__bf16)pe;
         }
@@ -264,13 +309,22 @@ void prefill_bf16_kernel(PrefillArgs a, int tq, int tiles) {
       }
       return over;
     };
-    auto move_reference = [&]() {
+    auto column_max = [&](int qc) {
+      float mx = kNegInf;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) mx = fmaxf(mx, e < 4 ? s0[qc][e] : s1[qc][e - 4]);
+      return max_xor16_32(mx) * sc;
+    };
+    // The wave's first step sets the reference before its weights (it would always move it);
+    // its sums and accumulators are still zero.
+    if (st == wlo) {
+#pragma unroll
+      for (int qc = 0; qc < QC; ++qc) m[qc] = fmaxf(m[qc], column_max(qc));
+    }
+    if (__builtin_amdgcn_ballot_w64(weights()) != 0) {
 #pragma unroll
       for (int qc = 0; qc < QC; ++qc) {
-        float mx = kNegInf;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, e < 4 ? s0[qc][e] : s1[qc][e - 4]);
-        const float cand = max_xor16_32(mx) * c;
+        const float cand = column_max(qc);
         const bool grow = cand > m[qc];
         const float alpha = grow ? fast_exp2(m[qc] - cand) : 1.0f;
         m[qc] = grow ? cand : m[qc];
@@ -278,11 +332,6 @@ void prefill_bf16_kernel(PrefillArgs a, int tq, int tiles) {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) acc[qc][nb] *= alpha;
       }
-    };
-    // The first step sets the reference before its weights (it would always move it).
-    if (st == 0) move_reference();
-    if (__builtin_amdgcn_ballot_w64(weights()) != 0) {
-      move_reference();
       weights();
     }
 #pragma unroll
@@ -293,24 +342,23 @@ void prefill_bf16_kernel(PrefillArgs a, int tq, int tiles) {
     // 16nb + 4(i mod 4) .. +3 of key row 4j4 + i/4, and lane c16 receives channel 16nb + c16 of
     // those four rows.
     u32x2 vr[2 * NB];
-    constexpr int HI = 16 * ROWB;   // rows 16.. of the tile
-    vr[0] = tr_read<0>(vaddr[0] + sb);
-    vr[1] = tr_read<HI>(vaddr[0] + sb);
-    vr[2] = tr_read<0>(vaddr[1] + sb);
-    vr[3] = tr_read<HI>(vaddr[1] + sb);
-    vr[4] = tr_read<0>(vaddr[2] + sb);
-    vr[5] = tr_read<HI>(vaddr[2] + sb);
-    vr[6] = tr_read<0>(vaddr[3] + sb);
-    vr[7] = tr_read<HI>(vaddr[3] + sb);
+    vr[0] = tr_read<0>(va[0] + sb);
+    vr[1] = tr_read<HALF>(va[0] + sb);
+    vr[2] = tr_read<0>(va[1] + sb);
+    vr[3] = tr_read<HALF>(va[1] + sb);
+    vr[4] = tr_read<0>(va[2] + sb);
+    vr[5] = tr_read<HALF>(va[2] + sb);
+    vr[6] = tr_read<0>(va[3] + sb);
+    vr[7] = tr_read<HALF>(va[3] + sb);
     if constexpr (NB == 8) {
-      vr[8] = tr_read<0>((vaddr[0] ^ 128u) + sb);
-      vr[9] = tr_read<HI>((vaddr[0] ^ 128u) + sb);
-      vr[10] = tr_read<0>((vaddr[1] ^ 128u) + sb);
-      vr[11] = tr_read<HI>((vaddr[1] ^ 128u) + sb);
-      vr[12] = tr_read<0>((vaddr[2] ^ 128u) + sb);
-      vr[13] = tr_read<HI>((vaddr[2] ^ 128u) + sb);
-      vr[14] = tr_read<0>((vaddr[3] ^ 128u) + sb);
-      vr[15] = tr_read<HI>((vaddr[3] ^ 128u) + sb);
+      vr[8] = tr_read<1024>(va[0] + sb);
+      vr[9] = tr_read<HALF + 1024>(va[0] + sb);
+      vr[10] = tr_read<1024>(va[1] + sb);
+      vr[11] = tr_read<HALF + 1024>(va[1] + sb);
+      vr[12] = tr_read<1024>(va[2] + sb);
+      vr[13] = tr_read<HALF + 1024>(va[2] + sb);
+      vr[14] = tr_read<1024>(va[3] + sb);
+      vr[15] = tr_read<HALF + 1024>(va[3] + sb);
       asm volatile("s_waitcnt lgkmcnt(0)"
                    : "+v"(vr[0]), "+v"(vr[1]), "+v"(vr[2]), "+v"(vr[3]), "+v"(vr[4]),
                      "+v"(vr[5]), "+v"(vr[6]), "+v"(vr[7]), "+v"(vr[8]), "+v"(vr[9]),
@@ -324,45 +372,37 @@ void prefill_bf16_kernel(PrefillArgs a, int tq, int tiles) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       const u32x4 w = {vr[2 * nb][0], vr[2 * nb][1], vr[2 * nb + 1][0], vr[2 * nb + 1][1]};
-      const bf16x8 va = __builtin_bit_cast(bf16x8, w);
 #pragma unroll
       for (int qc = 0; qc < QC; ++qc)
-        acc[qc][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pB[qc], acc[qc][nb], 0, 0, 0);
+        acc[qc][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w),
+                                                              pB[qc], acc[qc][nb], 0, 0, 0);
     }
-    rstage = rstage == STAGES - 1 ? 0 : rstage + 1;
     __builtin_amdgcn_sched_barrier(0);
-  };
+  }
 
-  // Steps whose 32 keys all lie in every position's support need no mask: they form one run
-  // [st_a, st_b); the steps before (a ragged interval start) and after (the causal diagonal)
-  // are masked.
-  int st_a = (mask_lo + 31) / 32 - s_first;
-  int st_b = (mask_hi + 1) / 32 - s_first;
-  st_a = max(0, min(st_a, nsteps));
-  st_b = max(st_a, min(st_b, nsteps));
-  for (int st = 0; st < st_a; ++st) step(st, std::true_type{});
-  for (int st = st_a; st < st_b; ++st) step(st, std::false_type{});
-  for (int st = st_b; st < nsteps; ++st) step(st, std::true_type{});
-
-  // Outputs: o = acc / l (bf16 RNE), lse = (m + log2 l) * ln 2.
+  // Outputs: o = acc / l (bf16 RNE), lse = (m + log2 l) * ln 2.  Lane (c16, j4) holds channels
+  // 16nb + 4j4 .. +3 of its column; a swap of neighbouring quarters gives each lane 8 consecutive
+  // channels of every second block, so that a store writes 16 bytes per lane.  (The columns are
+  // worked out again: kept across the key loop, they would cost registers that it needs.)
+  int ce = c16;
+  asm("" : "+v"(ce));
 #pragma unroll
   for (int qc = 0; qc < QC; ++qc) {
     const float l = sum_xor16_32(lsum[qc]);
-    if (!valid[qc]) continue;
     const float inv = 1.0f / l;
-    uint16_t* orow = (uint16_t*)a.out + ((size_t)(b * (size_t)n + tcol[qc]) * a.hq + hcol[qc]) * D;
+    u32x4 w[NB / 2];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      u32x2 w;
-      w[0] = (uint32_t)float_to_bf16_rne(acc[qc][nb][0] * inv) |
-             ((uint32_t)float_to_bf16_rne(acc[qc][nb][1] * inv) << 16);
-      w[1] = (uint32_t)float_to_bf16_rne(acc[qc][nb][2] * inv) |
-             ((uint32_t)float_to_bf16_rne(acc[qc][nb][3] * inv) << 16);
-      *(u32x2*)(orow + 16 * nb + 4 * j4) = w;
+    for (int q = 0; q < NB / 2; ++q) w[q] = pair_blocks(acc[qc][2 * q], acc[qc][2 * q + 1], inv);
+    const Column x = column(qc, ce);
+    if (x.valid) {
+      unsigned char* orow = (unsigned char*)a.out + row0 * ROWB + row_offset(x);
+#pragma unroll
+      for (int q = 0; q < NB / 2; ++q)
+        *(u32x4*)(orow + 64 * q + 32 * (j4 & 1) + 16 * (j4 >> 1)) = w[q];
+      if (a.lse != nullptr && j4 == 0)
+        a.lse[((size_t)b * a.hq + (size_t)(g * G + x.head)) * n + t0 + x.cp] =
+            (m[qc] + __builtin_log2f(l)) * 0.69314718055994531f;
     }
-    if (a.lse != nullptr && j4 == 0)
-      a.lse[((size_t)b * a.hq + hcol[qc]) * n + tcol[qc]] =
-          (m[qc] + __builtin_log2f(l)) * 0.69314718055994531f;
   }
 
   // Ring state after the prompt: positions max(0, n - slots) .. n-1 at slot s mod slots.
@@ -382,25 +422,30 @@ void prefill_bf16_kernel(PrefillArgs a, int tq, int tiles) {
   }
 }
 
-template <int D>
+template <int D, int ST, int OCC>
 hipError_t launch_prefill_d(const PrefillArgs& a, hipStream_t stream) {
-  constexpr int QC = D == 128 ? kPrefillColGroups128 : kPrefillColGroups64;
-  constexpr int NW = D == 128 ? kPrefillWaves128 : kPrefillWaves64;
-  constexpr int ST = D == 128 ? kPrefillStages128 : kPrefillStages64;
-  const int tq = 16 * QC * NW / a.group;
-  const int tiles = (a.n + tq - 1) / tq;
-  const size_t blocks = (size_t)a.batch * a.hkv * tiles;
-  if (blocks == 0) return hipSuccess;
+  PrefillPlan pl;
+  pl.tq = kPrefillCols / a.group;
+  pl.tiles = (a.n + pl.tq - 1) / pl.tq;
+  pl.by_tiles = FastDiv::make((uint32_t)pl.tiles);
+  pl.by_hkv = FastDiv::make((uint32_t)a.hkv);
+  pl.by_group = FastDiv::make((uint32_t)a.group);
+  pl.by_half = FastDiv::make((uint32_t)(a.mode == kSupportPBB ? a.block / 2 : 1));
+  const size_t blocks = (size_t)a.batch * a.hkv * pl.tiles;
   if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((prefill_bf16_kernel<D, QC, NW, ST>), dim3((unsigned)blocks),
-                     dim3(NW * 64), 0, stream, a, tq, tiles);
+  const int tph = a.mode == kSupportPBB ? a.block / 2 / pl.tq : pl.tiles;
+  pl.by_weight = blocks <= (size_t)kByWeightMaxBlocks && tph >= kByWeightMinPhases;
+  pl.order = TileOrder::make(pl.tiles, tph > 0 ? tph : 1, a.batch * a.hkv);
+  hipLaunchKernelGGL((prefill_bf16_kernel<D, ST, OCC>), dim3((unsigned)blocks),
+                     dim3(kPrefillWaves * 64), 0, stream, a, pl);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_prefill_bf16(const PrefillArgs& a, int32_t head_dim, hipStream_t stream) {
-  return head_dim == 128 ? launch_prefill_d<128>(a, stream) : launch_prefill_d<64>(a, stream);
+  return head_dim == 128 ? launch_prefill_d<128, kPrefillStages128, kPrefillOcc128>(a, stream)
+                         : launch_prefill_d<64, kPrefillStages64, kPrefillOcc64>(a, stream);
 }
 
 }  // namespace pbb

@@ -1,0 +1,76 @@
+"""Tile order and index arithmetic of the prefill launch.
+
+On the CPU: ``csrc/pbb_index.h`` compiled with g++ -- FastDiv against the division over edge and
+random dividends, TileOrder a permutation of every unit's tiles with falling weights.  On the GPU:
+prompts whose launches take the by-weight order (and its neighbours that do not), against the
+oracle: half-blocks that the tile length does not divide, cut last half-blocks, prompts within the
+first half-block, numbers of units that are no multiple of the 8 XCDs, and tiles some of whose
+waves skip steps or hold no position at all.
+"""
+from __future__ import annotations
+
+import os
+import subprocess
+
+import pytest
+
+from test_prefill import _cfg, _check
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+CHECK = r"""
+#include <cstdio>
+#include <random>
+#include <vector>
+#include "pbb_index.h"
+int main() {
+  std::mt19937 rng(5);
+  auto check = [](uint32_t d, int x) { return pbb::FastDiv::make(d).div(x) == (int)((uint32_t)x / d); };
+  for (int i = 0; i < 200000; ++i) {
+    const uint32_t d = i < 3000 ? i + 1 : 1 + (rng() >> (1 + rng() % 31)) % 0x7fffffffu;
+    const int m = 0x7fffffff, q = (int)(m / d) * d, r = (int)(rng() >> 1);
+    for (int x : {0, 1, (int)(d - 1), (int)(d < 0x7fffffffu ? d : 0), m, q, q > 0 ? q - 1 : 0, r})
+      if (!check(d, x)) return std::printf("div %u %d\n", d, x), 1;
+  }
+  for (int tph = 1; tph < 40; ++tph)
+    for (int tiles = 1; tiles < 200; ++tiles) {
+      const auto o = pbb::TileOrder::make(tiles, tph, 3);
+      std::vector<char> seen(tiles, 0);
+      int last = 1 << 30;
+      for (int k = 0; k < tiles; ++k) {
+        const int t = o.tile(k);
+        if (t < 0 || t >= tiles || seen[t]) return std::printf("tile %d %d %d\n", tph, tiles, k), 1;
+        seen[t] = 1;
+        const int w = t < tph ? t : tph + t % tph;
+        if (w > last) return std::printf("order %d %d %d\n", tph, tiles, k), 1;
+        last = w;
+      }
+    }
+  return 0;
+}
+"""
+
+
+def test_index_arithmetic(tmp_path):
+    src = tmp_path / "check.cpp"
+    src.write_text(CHECK)
+    exe = str(tmp_path / "check")
+    inc = os.path.join(ROOT, "paper_2606_02680_amd", "csrc")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", inc, str(src), "-o", exe], check=True)
+    p = subprocess.run([exe], capture_output=True, text=True)
+    assert p.returncode == 0, p.stdout
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode,batch,n,hq,hkv,d,block,window,slots", [
+    ("pbb", 3, 1021, 8, 2, 128, 2048, 0, 0),     # within the first half-block
+    ("pbb", 1, 1337, 6, 1, 64, 500, 0, 0),       # tiles of 21, half-blocks of 250: 11 phases
+    ("pbb", 5, 700, 5, 1, 128, 514, 0, 0),       # tiles of 25, half-blocks of 257
+    ("pbb", 2, 913, 16, 4, 64, 512, 0, 0),       # 8 phases exactly, a cut last half-block
+    ("pbb", 2, 913, 16, 4, 64, 510, 0, 0),       # 7 phases: in order
+    ("swa", 3, 450, 4, 1, 128, 0, 200, 200),
+    ("swa", 1, 130, 16, 1, 64, 0, 64, 70),       # tiles of 8 positions
+    ("pbb", 1, 33, 4, 4, 64, 64, 0, 0),          # G = 1: three of a tile's waves hold nothing
+])
+def test_prefill_orders(cuda, mode, batch, n, hq, hkv, d, block, window, slots):
+    _check(_cfg(mode, batch, n, hq, hkv, d, block, window, slots), n, cuda)
