@@ -70,7 +70,6 @@ int32_t decode_splits(const pbb_desc_t* d, bool swa) {
   const int64_t max_steps = ((int64_t)(swa ? d->window : d->block) + 31) / 32;
   int64_t s = std::min(kSplitUnits / units, (max_steps + 7) / 8);
   s = std::min<int64_t>(s, kSplitMaxWays);
-  s = std::min<int64_t>(s, pbb::kMaxSplitStates / (d->n_q_heads / d->n_kv_heads));
   return (int32_t)std::max<int64_t>(1, s);
 }
 

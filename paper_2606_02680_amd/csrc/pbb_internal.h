@@ -10,10 +10,6 @@ namespace pbb {
 
 enum SupportMode : int32_t { kSupportPBB = 0, kSupportSWA = 1 };
 
-// Largest number of (split, query head) states one unit of a split decode launch merges (the
-// merge stages their maxima and sums in LDS).
-constexpr int kMaxSplitStates = 2048;
-
 constexpr int32_t kMaxGroup = 16;         // query heads per KV head held by one MFMA tile
 constexpr int64_t kSplitMaxUnits = 64;    // bf16 decode launches with at most this many units split
 constexpr int64_t kSplitMaxWays = 8;      // workgroups per unit of a split launch, at most
@@ -62,7 +58,8 @@ struct DecodeArgs {
   // resets the counter to 0.
   int32_t splits;
   uint32_t* counters;  // [batch * hkv], zero between launches
-  float* ws_part;      // [batch * hkv][splits][group][head_dim + 2]
+  // [batch * hkv][splits] states: outputs [group][head_dim], then (maximum, sum) [group]
+  float* ws_part;
   // Turns per position of rotary channel pair c (angle / 2 pi), c < head_dim / 2.
   double rope_turns[64];
 };
