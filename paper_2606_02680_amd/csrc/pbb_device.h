@@ -69,29 +69,6 @@ __device__ __forceinline__ void wait_groups(int ahead) {
   }
 }
 
-// First source a(t) of the support of target t: PBB (mode 0) max(0, h(floor(t/h) - 1)) with
-// h = block/2 (Sec. 3 "Flash-PBB"), SWA max(0, t - window + 1) (Prop. 2).  Never decreases in t.
-__device__ __forceinline__ int support_start(int mode, int block, int window, int t) {
-  int lo;
-  if (mode == 0) {
-    const int h = block >> 1;
-    lo = h * (t / h - 1);
-  } else {
-    lo = t - window + 1;
-  }
-  return lo > 0 ? lo : 0;
-}
-
-// Last target whose support contains source s (the largest t with support_start(t) <= s):
-// PBB h(floor(s/h) + 2) - 1, SWA s + window - 1.
-__device__ __forceinline__ int support_last_target(int mode, int block, int window, int s) {
-  if (mode == 0) {
-    const int h = block >> 1;
-    return h * (s / h + 2) - 1;
-  }
-  return s + window - 1;
-}
-
 // Value of lane l ^ 16 and of lane l ^ 32 (gfx950 v_permlane16_swap / v_permlane32_swap with
 // both operands x: one result is the lane's own value, the other its partner's), on the VALU
 // instead of an LDS permute.
@@ -127,18 +104,20 @@ __device__ __forceinline__ u32x4 pair_blocks(f32x4 x, f32x4 y, float scale) {
   return u32x4{(uint32_t)s0[0], (uint32_t)s1[0], (uint32_t)s0[1], (uint32_t)s1[1]};
 }
 
-// LDS tiles of the prefill and backward kernels.  A 32-row tile (rows of D bf16) is stored as
-// [row / 8][128-byte line of the row][8 rows x 8 pieces of 16 bytes], one 1 KiB LDS DMA per block,
-// which reads whole cache lines; tile_block is the byte offset of row group y and line z.  Piece p
-// of a line of row r sits at slot 8 (r mod 8) + (p ^ tile_swz(r)).  Both reads of a tile are then
-// free of bank conflicts (64 banks; a 16-byte read serves per cycle the 16 lanes that share lane
-// bit 5 and the parity of lane bits 2..4, an 8-byte or transposed read the 32 lanes that share the
-// parity of lane bits 3..5), and a read's address is a lane constant for its piece within the line
-// (2 for row operands, 4 for transposed reads) plus an immediate.
+// LDS tiles of the prefill and backward kernels.  A 32-row tile (rows of D bf16) is stored in
+// 1 KiB blocks, one LDS DMA each, that hold whole rows (so that the DMA reads them contiguously):
+// 4 rows as [128-byte line][row][8 pieces of 16 bytes] at d = 128, 8 rows as [row][8 pieces] at
+// d = 64.  Piece p of a line of row r sits in slot p ^ tile_swz(r) of its eight.  Both reads of a
+// tile are then free of bank conflicts (64 banks; a 16-byte read serves per cycle the 16 lanes
+// that share lane bit 5 and the parity of lane bits 2..4, an 8-byte or transposed read the 32
+// lanes that share the parity of lane bits 3..5), and a read's address is a lane constant for its
+// piece within the line (2 for row operands, 4 for transposed reads) plus an immediate, where a
+// row-major tile with its swizzle across the row takes one address addition per read.
 template <int D>
-__device__ __forceinline__ constexpr int tile_block(int y, int z) {
-  return (y * (D / 64) + z) * 1024;
+__device__ __forceinline__ constexpr int tile_row(int r) {
+  return D == 128 ? (r >> 2) * 1024 + (r & 3) * 128 : r * 128;
 }
+constexpr int kTileLine = 512;   // from a row's first line to its second (d = 128)
 __device__ __forceinline__ constexpr int tile_swz(int r) { return r & 6; }
 
 // One 16-byte LDS DMA (global_load_lds) from a wave-uniform base plus a 32-bit lane offset, so
@@ -147,6 +126,46 @@ __device__ __forceinline__ constexpr int tile_swz(int r) { return r & 6; }
 __device__ __forceinline__ void dma16(const unsigned char* base, uint32_t off, unsigned char* lds) {
   __builtin_amdgcn_global_load_lds((const void*)(base + off),
                                    (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+}
+
+// DMA of 16 rows of a tensor into half a tile, 1 KiB per instruction.  dma_offsets: this lane's
+// byte offsets from the first row (`stride` bytes between rows).  dma_rows16: the rows from the
+// wave-uniform address p, of which `left` more than the first exist (rows past them read the last
+// one instead; negative: p itself lies past it).  Callers step p along, so that a step's loads
+// cost no multiplication: the scalar work of an issue stands in every wave's serial step (with a
+// multiplication and a limit per block, some 40 more scalar instructions per step, the d = 128
+// kernels of the backward were 2 to 3 % slower).
+template <int D>
+constexpr int kDmaBlocks = D / 64;   // blocks of 8 rows
+
+template <int D>
+__device__ __forceinline__ void dma_offsets(int lane, uint32_t stride, uint32_t (&off)[kDmaBlocks<D>]) {
+#pragma unroll
+  for (int y = 0; y < kDmaBlocks<D>; ++y) {
+    const int r = D == 128 ? 4 * y + ((lane >> 3) & 3) : lane >> 3;
+    const int line = D == 128 ? lane >> 5 : 0;
+    off[y] = (uint32_t)r * stride + (uint32_t)(128 * line + (((lane & 7) ^ tile_swz(r)) << 4));
+  }
+}
+
+template <int D>
+__device__ __forceinline__ void dma_rows16(const unsigned char* p, int left, uint32_t stride,
+                                           const uint32_t (&off)[kDmaBlocks<D>],
+                                           unsigned char* lds) {
+  constexpr int N = kDmaBlocks<D>;
+  if (left >= 15) {
+#pragma unroll
+    for (int y = 0; y < 2 * N; ++y)
+      dma16(y < N ? p : p + (size_t)stride * 8, off[y % N], lds + 1024 * y);
+  } else {
+#pragma unroll
+    for (int y = 0; y < 2 * N; ++y) {
+      const int r0 = y < N ? 0 : 8;   // first row of the block's eight, and the rows after it
+      const unsigned char* q = p + (int64_t)min(left, r0) * (int64_t)stride;
+      const uint32_t lim = (uint32_t)max(left - r0, 0) * stride + (uint32_t)(2 * D - 16);
+      dma16(q, min(off[y % N], lim), lds + 1024 * y);
+    }
+  }
 }
 
 // Transposed LDS read (gfx950 ds_read_b64_tr_b16) at addr + OFF.  Issued as inline asm: the
@@ -159,6 +178,67 @@ __device__ __forceinline__ u32x2 tr_read(uint32_t addr) {
   u32x2 r;
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "i"(OFF));
   return r;
+}
+
+// This lane's LDS byte addresses in a 32-row tile at `base`, for 16x16 products.  Row operand of
+// 32-channel slice kk (row c16, piece 4kk + j4): ra[kk mod 2] + kTileLine (kk / 2); rows 16..
+// 32 D bytes further on.  Transposed reads of 16-channel chunk nb (row 4j4 + c16/4, channels
+// 16nb + 4(c16 mod 4) .. +3): ta[nb mod 4] + kTileLine (nb / 4); rows 16.. 32 D bytes further on.
+template <int D>
+__device__ __forceinline__ void tile_addresses(uint32_t base, int c16, int j4, uint32_t (&ra)[2],
+                                               uint32_t (&ta)[4]) {
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+    ra[x] = base + tile_row<D>(c16) + (((4 * x + j4) ^ tile_swz(c16)) << 4);
+  const int r = 4 * j4 + (c16 >> 2);
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+    ta[x] = base + tile_row<D>(r) + (((2 * x + ((c16 & 3) >> 1)) ^ tile_swz(r)) << 4) +
+            ((c16 & 1) << 3);
+}
+
+// The transposed operands of a 32-row tile at offset OFF: dst[2nb] holds rows 4j4 .. +3 and
+// dst[2nb + 1] rows 16 + 4j4 .. +3 of channel 16nb + c16 (the row order of a 16x16 result pair's
+// registers).  wait_chunks waits for every LDS read issued so far; its operands make uses follow.
+template <int D, int OFF>
+__device__ __forceinline__ void read_chunks(u32x2 (&dst)[D / 8], const uint32_t (&ta)[4], uint32_t sb) {
+  constexpr int H = 32 * D;
+  dst[0] = tr_read<OFF>(ta[0] + sb);
+  dst[1] = tr_read<OFF + H>(ta[0] + sb);
+  dst[2] = tr_read<OFF>(ta[1] + sb);
+  dst[3] = tr_read<OFF + H>(ta[1] + sb);
+  dst[4] = tr_read<OFF>(ta[2] + sb);
+  dst[5] = tr_read<OFF + H>(ta[2] + sb);
+  dst[6] = tr_read<OFF>(ta[3] + sb);
+  dst[7] = tr_read<OFF + H>(ta[3] + sb);
+  if constexpr (D == 128) {
+    dst[8] = tr_read<OFF + kTileLine>(ta[0] + sb);
+    dst[9] = tr_read<OFF + H + kTileLine>(ta[0] + sb);
+    dst[10] = tr_read<OFF + kTileLine>(ta[1] + sb);
+    dst[11] = tr_read<OFF + H + kTileLine>(ta[1] + sb);
+    dst[12] = tr_read<OFF + kTileLine>(ta[2] + sb);
+    dst[13] = tr_read<OFF + H + kTileLine>(ta[2] + sb);
+    dst[14] = tr_read<OFF + kTileLine>(ta[3] + sb);
+    dst[15] = tr_read<OFF + H + kTileLine>(ta[3] + sb);
+  }
+}
+
+__device__ __forceinline__ bf16x8 join_chunks(u32x2 x, u32x2 y) {
+  const u32x4 w = {x[0], x[1], y[0], y[1]};
+  return __builtin_bit_cast(bf16x8, w);
+}
+
+template <int D>
+__device__ __forceinline__ void wait_chunks(u32x2 (&v)[D / 8]) {
+  if constexpr (D == 128)
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]),
+                   "+v"(v[6]), "+v"(v[7]), "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]),
+                   "+v"(v[12]), "+v"(v[13]), "+v"(v[14]), "+v"(v[15]));
+  else
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]),
+                   "+v"(v[6]), "+v"(v[7]));
 }
 
 }  // namespace pbb

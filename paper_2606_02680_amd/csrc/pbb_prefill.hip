@@ -21,15 +21,15 @@
 // positions that fall in the last `slots` positions of the prompt into the ring (slot s mod slots,
 // Appendix F.1), the state decode continues from.
 //
-// LDS tiles: tile_block() and tile_swz() in pbb_device.h.
+// LDS tiles: tile_row() and tile_swz() in pbb_device.h.
 //
 // Bound: instruction issue (matrix and vector work of a SIMD overlap only in part; at c3's heads
 // the matrix cores draw the card's power limit as well).  What a tile costs beside its key steps
 // counts at d = 64 and small blocks, where it walks 3 to 5 of them: index arithmetic by FastDiv
 // instead of divisions, packed conversions and 16-byte stores in the epilogue, steps skipped per
-// wave, and LDS addresses that are two or four lane constants plus immediates took the paper's
-// shape (12/2 heads, d 64, B 128, n 65536; 238 MB) from 74.1 to 61.4 us (3.9 TB/s) and c3's heads
-// (n 16384, batch 4) from 1533 to 1491 us (1060 TFLOP/s).  32x32x16 matrix instructions in the
+// wave, scalar-stepped tile addresses and LDS addresses that are two or four lane constants plus
+// immediates took the paper's shape (12/2 heads, d 64, B 128, n 65536; 238 MB) from 74.1 to 61.4
+// us (3.9 TB/s) and c3's heads (n 16384, batch 4) from 1529 to 1485 us (1065 TFLOP/s).  32x32x16 matrix instructions in the
 // same structure (32 columns at once, a fifth fewer vector instructions) measured 1574 us there
 // and 62.0 at the paper's shape.
 
@@ -54,44 +54,21 @@ constexpr int kPrefillStages64 = 4, kPrefillOcc64 = 4;
 // Starting reference of the running maximum (log2 units): finite and below any score.
 constexpr float kNoScore = -1.0e30f;
 
-// Launches of at most kByWeightMaxBlocks workgroups (16 per CU), with at least kByWeightMinPhases
-// tiles per half-block (SWA: per prompt), deal out their tiles heaviest first instead of in order.
-// In order, a CU's few workgroups often have the same phase (with 32 tiles per unit, the 32 CUs of
-// an XCD each take one tile index of every unit) and the launch waits for the CUs with the longest
-// intervals; with many workgroups per CU that evens out, and tiles in order share their keys in
-// an XCD's L2.  Measured, by weight against in order, 32/8 heads, d 128, B 2048: batch 3, n 1021
-// (768 workgroups) 36.1 against 49.1 us; batch 1, n 2000 54.8 / 58.7; batch 4, n 2048 146 / 165;
-// batch 4, n 4096 (4096) 341 / 347; batch 4, n 8192 (8192) 839 / 721.  16/4 heads, d 64, B 512 (8
-// tiles per half-block): batch 8, n 500 15.1 / 17.5, batch 4, n 8192 (4096) 81.9 / 81.5.  12/2
-// heads, d 64, B 128 (3 tiles per half-block, which mix anyway): n 16384 20.8 / 18.7.
-constexpr int kByWeightMaxBlocks = 4096;
-constexpr int kByWeightMinPhases = 8;
-
-// Launch constants: positions per tile, tiles per unit and the divisors of the index arithmetic.
-struct PrefillPlan {
-  int tq;
-  int tiles;
-  int by_weight;   // 1: tiles are dealt out by weight (order)
-  FastDiv by_tiles, by_hkv, by_group, by_half;
-  TileOrder order;
-};
-
 template <int D, int ST, int OCC>
 __global__ __launch_bounds__(kPrefillWaves * 64) __attribute__((amdgpu_waves_per_eu(OCC)))
-void prefill_bf16_kernel(PrefillArgs a, PrefillPlan pl) {
+void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
   constexpr int NW = kPrefillWaves;
   constexpr int QC = kPrefillGroups;
   constexpr int KK = D / 32;            // 32-channel slices of the score contraction
   constexpr int NB = D / 16;            // 16-channel blocks of the output
   constexpr int ROWB = D * 2;           // bytes of one K or V row
   constexpr int PPR = D / 8;            // 16-byte pieces per row
-  constexpr int LN = D / 64;            // 128-byte lines per row
   constexpr int HALF = 16 * ROWB;       // 16 rows of a tile
   constexpr int TILE = 2 * HALF;
   constexpr int BUF = 2 * TILE;         // K tile, then V tile
   constexpr int STAGES = ST;
   static_assert(STAGES >= 3, "stages");
-  constexpr int WROWS = 64 / NW;        // rows of one tensor that a wave loads per step
+  static_assert(NW == 4, "one (tensor, 16-row half) of a step per wave");
   __shared__ __align__(1024) unsigned char smem[STAGES * BUF];
 
   const int tid = threadIdx.x;
@@ -103,29 +80,9 @@ void prefill_bf16_kernel(PrefillArgs a, PrefillPlan pl) {
   const int n = a.n;
 
   // First source of the support of target t.
-  auto support_lo = [&](int t) -> int {
-    const int lo = a.mode == kSupportPBB ? (a.block >> 1) * (pl.by_half.div(t) - 1)
-                                         : t - a.window + 1;
-    return max(lo, 0);
-  };
-
-  // Workgroup i runs on XCD i mod 8.
-  const int nblk = gridDim.x;
+  auto support_lo = [&](int t) -> int { return pl.support_lo(t, a.block, a.window); };
   int bg, tile;
-  if (pl.by_weight) {
-    const int rank = pl.order.by_units.div(blockIdx.x);
-    bg = blockIdx.x - rank * (int)pl.order.by_units.d;
-    tile = pl.order.tile(rank);
-  } else {
-    // Give each XCD a contiguous run of tiles so that tiles sharing keys (neighbours of one
-    // sequence and KV head) share that XCD's L2.
-    const int per = nblk >> 3, rem = nblk & 7;
-    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-    const int tile_id =
-        (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + local;
-    bg = pl.by_tiles.div(tile_id);
-    tile = tile_id - bg * pl.tiles;
-  }
+  pl.locate((int)blockIdx.x, (int)gridDim.x, bg, tile);
   const int b = pl.by_hkv.div(bg);
   const int g = bg - b * a.hkv;
   const int t0 = tile * pl.tq;
@@ -164,47 +121,29 @@ void prefill_bf16_kernel(PrefillArgs a, PrefillPlan pl) {
     for (int kk = 0; kk < KK; ++kk) qB[qc][kk] = *(const bf16x8*)(qbase + (off + 64u * kk));
   }
 
-  // DMA of a step: each wave loads WROWS rows of K (the first half of the waves) or V, 128 bytes
-  // of 8 rows per instruction: lane l takes row l / 8 and the piece that belongs at slot l, addressed as a
-  // wave-uniform base plus a 32-bit lane offset.  In the last step, rows past t_last read row
-  // t_last instead (inside the tensor; masked for every column).
-  const unsigned char* const wsrc = wave >= NW / 2 ? vbase : kbase;
-  const int wrow = WROWS * (wave % (NW / 2));
-  const uint32_t doff = (uint32_t)(lane >> 3) * rowstride +
-                        (uint32_t)(((lane & 7) ^ tile_swz(lane >> 3)) << 4);
-  auto issue = [&](int stage, int st) {
-    unsigned char* dst = smem + stage * BUF + wave * WROWS * ROWB;
-#pragma unroll
-    for (int y = 0; y < WROWS / 8; ++y) {
-      const int r0 = min((s_first + st) * 32 + wrow + 8 * y, t_last);
-      const unsigned char* src = wsrc + (size_t)r0 * rowstride;
-      const uint32_t off = min(doff, (uint32_t)min(t_last - r0, 7) * rowstride + 112u);
-#pragma unroll
-      for (int z = 0; z < LN; ++z) dma16(src + 128 * z, off, dst + tile_block<D>(y, z));
-    }
+  // DMA of a step: wave w loads 16 rows (half w & 1) of K (w < 2) or V.  In the last step, rows
+  // past t_last read row t_last instead (inside the tensor; masked for every column).
+  const int wrow = s_first * 32 + 16 * (wave & 1);
+  const unsigned char* src = (wave >= 2 ? vbase : kbase) + (size_t)wrow * rowstride;
+  int left = t_last - wrow;
+  uint32_t doff[kDmaBlocks<D>];
+  dma_offsets<D>(lane, rowstride, doff);
+  auto issue = [&](int stage) {   // the next step
+    dma_rows16<D>(src, left, rowstride, doff, smem + stage * BUF + wave * HALF);
+    src += (size_t)rowstride * 32;
+    left -= 32;
   };
 
   // Steps 0 .. STAGES-2 go out first; step st then issues step st + STAGES - 1.
 #pragma unroll
   for (int s = 0; s < STAGES - 1; ++s)
-    if (s < nsteps) issue(s, s);
+    if (s < nsteps) issue(s);
 
-  // LDS byte addresses of this lane's reads in stage 0.  Row operand of slice kk: row c16, piece
-  // 4kk + j4: ra[kk mod 2] + 1024 (kk / 2); rows 16.. HALF further on.  Transposed reads of the
-  // values of chunk nb: row 4j4 + c16/4, channels 16nb + 4(c16 mod 4) .. +3:
-  // va[nb mod 4] + 1024 (nb / 4); rows 16.. HALF further on.
+  // LDS byte addresses of this lane's reads in stage 0 (tile_addresses; the V tile is TILE on).
   uint32_t ra[2], va[4];
   {
     const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-      ra[x] = base + tile_block<D>(c16 >> 3, 0) + (c16 & 7) * 128 +
-              (((4 * x + j4) ^ tile_swz(c16)) << 4);
-    const int vr = 4 * j4 + (c16 >> 2);
-#pragma unroll
-    for (int x = 0; x < 4; ++x)
-      va[x] = base + TILE + tile_block<D>(vr >> 3, 0) + (vr & 7) * 128 +
-              (((2 * x + ((c16 & 3) >> 1)) ^ tile_swz(vr)) << 4) + ((c16 & 1) << 3);
+    tile_addresses<D>(base, c16, j4, ra, va);
   }
   const __attribute__((address_space(3))) unsigned char* lds0 = nullptr;
 
@@ -237,7 +176,7 @@ void prefill_bf16_kernel(PrefillArgs a, PrefillPlan pl) {
     for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(qB[qc][kk]));
 
   int rstage = 0;
-  constexpr int OPS = WROWS / 8 * LN;           // DMA instructions of a wave per step
+  constexpr int OPS = D / 32;           // DMA instructions of a wave per step
 
   for (int st = 0; st < nsteps; ++st) {
     // This wave's loads of step st have landed once at most the loads of the steps issued
@@ -246,7 +185,7 @@ void prefill_bf16_kernel(PrefillArgs a, PrefillPlan pl) {
     wait_groups<STAGES - 2, OPS>(min(STAGES - 2, nsteps - 1 - st));
     lds_barrier();
     if (st + STAGES - 1 < nsteps)
-      issue(rstage == 0 ? STAGES - 1 : rstage - 1, st + STAGES - 1);
+      issue(rstage == 0 ? STAGES - 1 : rstage - 1);
     __builtin_amdgcn_sched_barrier(0);
     const uint32_t sb = (uint32_t)(rstage * BUF);
     rstage = rstage == STAGES - 1 ? 0 : rstage + 1;
@@ -260,7 +199,7 @@ void prefill_bf16_kernel(PrefillArgs a, PrefillPlan pl) {
     }
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      const auto* kp = lds0 + ra[kk & 1] + sb + 1024 * (kk >> 1);
+      const auto* kp = lds0 + ra[kk & 1] + sb + kTileLine * (kk >> 1);
       const bf16x8 ka = *(const __attribute__((address_space(3))) bf16x8*)(kp);
       const bf16x8 kb = *(const __attribute__((address_space(3))) bf16x8*)(kp + HALF);
 #pragma unroll
@@ -342,40 +281,14 @@ void prefill_bf16_kernel(PrefillArgs a, PrefillPlan pl) {
     // 16nb + 4(i mod 4) .. +3 of key row 4j4 + i/4, and lane c16 receives channel 16nb + c16 of
     // those four rows.
     u32x2 vr[2 * NB];
-    vr[0] = tr_read<0>(va[0] + sb);
-    vr[1] = tr_read<HALF>(va[0] + sb);
-    vr[2] = tr_read<0>(va[1] + sb);
-    vr[3] = tr_read<HALF>(va[1] + sb);
-    vr[4] = tr_read<0>(va[2] + sb);
-    vr[5] = tr_read<HALF>(va[2] + sb);
-    vr[6] = tr_read<0>(va[3] + sb);
-    vr[7] = tr_read<HALF>(va[3] + sb);
-    if constexpr (NB == 8) {
-      vr[8] = tr_read<1024>(va[0] + sb);
-      vr[9] = tr_read<HALF + 1024>(va[0] + sb);
-      vr[10] = tr_read<1024>(va[1] + sb);
-      vr[11] = tr_read<HALF + 1024>(va[1] + sb);
-      vr[12] = tr_read<1024>(va[2] + sb);
-      vr[13] = tr_read<HALF + 1024>(va[2] + sb);
-      vr[14] = tr_read<1024>(va[3] + sb);
-      vr[15] = tr_read<HALF + 1024>(va[3] + sb);
-      asm volatile("s_waitcnt lgkmcnt(0)"
-                   : "+v"(vr[0]), "+v"(vr[1]), "+v"(vr[2]), "+v"(vr[3]), "+v"(vr[4]),
-                     "+v"(vr[5]), "+v"(vr[6]), "+v"(vr[7]), "+v"(vr[8]), "+v"(vr[9]),
-                     "+v"(vr[10]), "+v"(vr[11]), "+v"(vr[12]), "+v"(vr[13]), "+v"(vr[14]),
-                     "+v"(vr[15]));
-    } else {
-      asm volatile("s_waitcnt lgkmcnt(0)"
-                   : "+v"(vr[0]), "+v"(vr[1]), "+v"(vr[2]), "+v"(vr[3]), "+v"(vr[4]),
-                     "+v"(vr[5]), "+v"(vr[6]), "+v"(vr[7]));
-    }
+    read_chunks<D, TILE>(vr, va, sb);
+    wait_chunks<D>(vr);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const u32x4 w = {vr[2 * nb][0], vr[2 * nb][1], vr[2 * nb + 1][0], vr[2 * nb + 1][1]};
+      const bf16x8 vt = join_chunks(vr[2 * nb], vr[2 * nb + 1]);
 #pragma unroll
       for (int qc = 0; qc < QC; ++qc)
-        acc[qc][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w),
-                                                              pB[qc], acc[qc][nb], 0, 0, 0);
+        acc[qc][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt, pB[qc], acc[qc][nb], 0, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -424,18 +337,10 @@ void prefill_bf16_kernel(PrefillArgs a, PrefillPlan pl) {
 
 template <int D, int ST, int OCC>
 hipError_t launch_prefill_d(const PrefillArgs& a, hipStream_t stream) {
-  PrefillPlan pl;
-  pl.tq = kPrefillCols / a.group;
-  pl.tiles = (a.n + pl.tq - 1) / pl.tq;
-  pl.by_tiles = FastDiv::make((uint32_t)pl.tiles);
-  pl.by_hkv = FastDiv::make((uint32_t)a.hkv);
-  pl.by_group = FastDiv::make((uint32_t)a.group);
-  pl.by_half = FastDiv::make((uint32_t)(a.mode == kSupportPBB ? a.block / 2 : 1));
+  const TilePlan pl = TilePlan::make(a.batch, a.hkv, a.group, a.n, a.mode == kSupportPBB, a.block,
+                                     kPrefillCols / a.group);
   const size_t blocks = (size_t)a.batch * a.hkv * pl.tiles;
   if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
-  const int tph = a.mode == kSupportPBB ? a.block / 2 / pl.tq : pl.tiles;
-  pl.by_weight = blocks <= (size_t)kByWeightMaxBlocks && tph >= kByWeightMinPhases;
-  pl.order = TileOrder::make(pl.tiles, tph > 0 ? tph : 1, a.batch * a.hkv);
   hipLaunchKernelGGL((prefill_bf16_kernel<D, ST, OCC>), dim3((unsigned)blocks),
                      dim3(kPrefillWaves * 64), 0, stream, a, pl);
   return hipGetLastError();

@@ -1,9 +1,9 @@
-"""Tile order and index arithmetic of the prefill launch.
+"""Tile order, step ranges and index arithmetic of the prefill and backward launches.
 
 On the CPU: ``csrc/pbb_index.h`` compiled with g++ -- FastDiv against the division over edge and
 random dividends, TileOrder a permutation of every unit's tiles with falling weights.  On the GPU:
 prompts whose launches take the by-weight order (and its neighbours that do not), against the
-oracle: half-blocks that the tile length does not divide, cut last half-blocks, prompts within the
+oracle (the backward's dq launch shares them): half-blocks that the tile length does not divide, cut last half-blocks, prompts within the
 first half-block, numbers of units that are no multiple of the 8 XCDs, and tiles some of whose
 waves skip steps or hold no position at all.
 """
@@ -14,7 +14,8 @@ import subprocess
 
 import pytest
 
-from test_prefill import _cfg, _check
+from tests.test_backward import _check_all, _run
+from tests.test_prefill import _cfg, _check
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -74,3 +75,17 @@ def test_index_arithmetic(tmp_path):
 ])
 def test_prefill_orders(cuda, mode, batch, n, hq, hkv, d, block, window, slots):
     _check(_cfg(mode, batch, n, hq, hkv, d, block, window, slots), n, cuda)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode,batch,n,hq,hkv,d,block,window", [
+    ("pbb", 3, 421, 8, 2, 128, 512, 0),       # dealt out by weight, cut last half-block
+    ("pbb", 1, 173, 10, 2, 64, 96, 0),        # h 48: key tiles across half-blocks
+    ("pbb", 2, 65, 4, 4, 128, 2, 0),          # one key past a tile; every step masked
+    ("pbb", 1, 17, 16, 1, 64, 64, 0),         # waves without keys or targets
+    ("swa", 1, 300, 6, 1, 128, 0, 45),        # windows that end inside a wave's keys
+    ("swa", 2, 129, 4, 2, 64, 0, 4096),
+])
+def test_backward_orders(cuda, mode, batch, n, hq, hkv, d, block, window):
+    got, ref, inputs = _run(mode, batch, n, hq, hkv, d, block, window, cuda)
+    _check_all(f"{mode} n={n} hq={hq} hkv={hkv} d={d}", mode, inputs, got, ref, block, window)
