@@ -95,7 +95,8 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
   const unsigned char* vbase = (const unsigned char*)a.v + ((size_t)b * n * a.hkv + g) * ROWB;
 
   // This lane's query columns: column col -> position t0 + col / G, head g*G + col % G.  Columns
-  // past the tile's positions repeat its last position and are never stored.
+  // past the tile's positions get zero queries and see no key of a masked step (tcol -1); they
+  // load the last position's row, and nothing of them is stored.
   const size_t row0 = ((size_t)b * n + t0) * a.hq + (size_t)g * G;   // row of (t0, head g*G)
   struct Column {
     int cp, head;   // position within the tile (the last one for columns past it), query head
@@ -113,8 +114,8 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
 #pragma unroll
   for (int qc = 0; qc < QC; ++qc) {
     const Column x = column(qc, c16);
-    tcol[qc] = t0 + x.cp;
-    lo_c[qc] = support_lo(tcol[qc]);
+    tcol[qc] = x.valid ? t0 + x.cp : -1;
+    lo_c[qc] = support_lo(t0 + x.cp);
     const uint32_t off = row_offset(x) + 16 * j4;
     const unsigned char* qbase = (const unsigned char*)a.q + row0 * ROWB;
 #pragma unroll
@@ -149,13 +150,18 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
 
   // The wave's own range of steps [wlo, whi] (its columns' positions tw_lo .. tw_hi), and the
   // run [ua, ub) of them whose keys all lie in every column's support (a(t) never decreases).
+  // A wave with columns past the tile's positions (`cut`) masks the steps that the tile's first
+  // position does not see whole.  Zero queries, and this run of the tile alone, make what such a
+  // column adds to the wave's vote on the softmax references below independent of any query.
   const int tw_lo = t0 + pl.by_group.div(wave * 16 * QC);
-  const int tw_hi = min(t0 + pl.by_group.div(wave * 16 * QC + 16 * QC - 1), t_last);
+  const int tw_end = t0 + pl.by_group.div(wave * 16 * QC + 16 * QC - 1);
+  const bool cut = tw_end > t_last;
+  const int tw_hi = min(tw_end, t_last);
   const int a_hi = support_lo(tw_hi);
   const int wlo = tw_lo <= t_last ? (support_lo(tw_lo) >> 5) - s_first : nsteps;
   const int whi = (tw_hi >> 5) - s_first;
   const int ua = ((a_hi + 31) >> 5) - s_first;
-  const int ub = ((tw_lo + 1) >> 5) - s_first;
+  const int ub = (((cut ? t0 : tw_lo) + 1) >> 5) - s_first;
 
   // m starts at a finite floor below any score, so that a column whose keys are all masked so
   // far gets exp2(-inf - m) = 0 without a separate test; its first real maximum always moves m.
@@ -174,6 +180,14 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
   for (int qc = 0; qc < QC; ++qc)
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(qB[qc][kk]));
+  if (cut) {
+#pragma unroll
+    for (int qc = 0; qc < QC; ++qc)
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk)
+        qB[qc][kk] = __builtin_bit_cast(
+            bf16x8, tcol[qc] >= 0 ? __builtin_bit_cast(u32x4, qB[qc][kk]) : u32x4{0u, 0u, 0u, 0u});
+  }
 
   int rstage = 0;
   constexpr int OPS = D / 32;           // DMA instructions of a wave per step
