@@ -432,22 +432,20 @@ void bwd_dkdv_kernel(BackwardArgs a, DkdvPlan pl) {
     // The dout^T reads for dv go out now, under the softmax arithmetic.
     u32x2 gr[2 * NB];
     read_chunks<D, TILE>(gr, ta, sb);
-    // Pairs outside the support score -inf and get p = 0.  Element e of s0 is target
-    // q0 + 4 j4 + e, of s1 target q0 + 16 + 4 j4 + e.
-    if constexpr (decltype(masked)::value) {
-      const int q0 = s0k + 32 * jc + 4 * j4;
-      const int lo = key - q0, up = t_hi - q0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        s0[e] = e >= lo && e <= up ? s0[e] : kNegInf;
-        s1[e] = 16 + e >= lo && 16 + e <= up ? s1[e] : kNegInf;
-      }
-    }
     bf16x8 pB, dsB;
+    // Pairs outside the support get p = 0 whatever their target's log-partition is: it is their
+    // exponent that is replaced (a score of -inf would give NaN where the log-partition is NaN or
+    // -inf).  Element e of s0 is target q0 + 4 j4 + e, of s1 target q0 + 16 + 4 j4 + e.
+    const int q0 = s0k + 32 * jc + 4 * j4;
+    const int lo = key - q0, up = t_hi - q0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float pe = fast_exp2(
-          __builtin_fmaf(e < 4 ? s0[e] : s1[e - 4], c, -(e < 4 ? l0[e] : l1[e - 4])));
+      float x = __builtin_fmaf(e < 4 ? s0[e] : s1[e - 4], c, -(e < 4 ? l0[e] : l1[e - 4]));
+      if constexpr (decltype(masked)::value) {
+        const int t = e < 4 ? e : 12 + e;
+        x = t >= lo && t <= up ? x : kNegInf;
+      }
+      const float pe = fast_exp2(x);
       pB[e] = (__bf16)pe;
       dsB[e] = (__bf16)(pe * (e < 4 ? d0[e] : d1[e - 4]));
     }

@@ -44,3 +44,39 @@ def test_prefill_cut_tile_heads(cuda, d, hq, block, window, n):
     assert not torch.equal(o0[:, n - 1, :2], o1[:, n - 1, :2])
     assert (bits(o0[:, n - 1, 2:]) == bits(o1[:, n - 1, 2:])).all()
     assert torch.equal(l0[:, 2:, n - 1], l1[:, 2:, n - 1])
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("-inf")])
+@pytest.mark.parametrize("d,hq,block,window,n,t", [
+    (128, 4, 256, 0, 300, 140),      # keys after the target and before its support share its steps
+    (64, 6, 64, 0, 200, 75),
+    (64, 4, 0, 45, 200, 110),
+])
+def test_backward_bad_log_partition(cuda, d, hq, block, window, n, t, value):
+    """A target whose log-partition is NaN or -inf: dk and dv of the keys outside its support keep
+    their bits (pairs outside the support weigh exactly 0)."""
+    g = torch.Generator().manual_seed(6)
+    q, do = (torch.randn(2, n, hq, d, generator=g).to(cuda, torch.bfloat16) for _ in range(2))
+    k, v = (torch.randn(2, n, 2, d, generator=g).to(cuda, torch.bfloat16) for _ in range(2))
+    if window:
+        desc = P.make_desc(2, hq, 2, d, window=window)
+        fwd, bwd, lo = P.swa_prefill, P.swa_backward, max(0, t - window + 1)
+    else:
+        desc, h = P.make_desc(2, hq, 2, d, block=block), block // 2
+        fwd, bwd, lo = P.pbb_prefill, P.pbb_backward, max(0, h * (t // h - 1))
+    out = torch.empty_like(q)
+    lse = torch.empty((2, hq, n), dtype=torch.float32, device=cuda)
+    fwd(desc, q, k, v, out, lse=lse)
+    grads = []
+    for bad in (False, True):
+        if bad:
+            lse[:, :, t] = value
+        dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
+        print(f"[isolation] backward {d} {hq} {block} {window} {n} {value if bad else ''}", flush=True)
+        bwd(desc, q, k, v, out, do, lse, dq, dk, dv)
+        torch.cuda.synchronize()
+        grads.append((dk, dv))
+    for a, b in zip(*grads):
+        assert not torch.isfinite(b[:, t]).all()
+        for keys in (slice(0, lo), slice(t + 1, n)):
+            assert torch.equal(a[:, keys], b[:, keys])
