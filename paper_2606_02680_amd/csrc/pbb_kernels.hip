@@ -123,8 +123,9 @@ __global__ void ring_fill_kernel(const int32_t* __restrict__ pos, const uint4* _
 // Bound: HBM.  Lane s of a stream takes channels 64 y + 4 s .. +3, so that each load instruction
 // reads whole 128-byte lines (with 32 contiguous bytes per lane, two instructions share every
 // line, and non-temporal loads fetched it twice: 885 us where temporal ones took 557).  Measured
-// against one key at a time with room for four heads: batch 512, 8 heads, d 128, B 1024
-// 554 -> 507 us (6.4 TB/s), batch 64, 8 heads, d 64, B 512 (cache-resident) 29.8 -> 23.0 us.
+// against one key at a time with room for four heads (20-step graphs): batch 512, 8 heads, d 128,
+// B 1024 553 -> 495 us (6.5 TB/s), batch 64, 8 heads, d 64, B 512 (cache-resident) 23.6 -> 18.5 us,
+// one sequence of 8 heads, d 128, B 2048 37.4 -> 15.5 us.
 
 // A vector load of ring data, non-temporal (NT) when the rings exceed the last-level cache.
 template <bool NT, typename T>
@@ -213,6 +214,16 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(DecodeArgs a) {
     float p[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) p[u] = fast_exp2(s[u] - mn);
+    // Masked keys add nothing, also where v_new is infinite (0 * inf).  Only a stream's last keys
+    // can be masked: selects in every iteration cost registers (101 against 78 at d = 128) and 18.2
+    // us where this branch takes 15.5 (one sequence, 8 heads, d 128, B 2048).
+    if (i0 + 16 * (U - 1) >= n_total) {
+#pragma unroll
+      for (int u = 1; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < E / 4; ++e)
+          vf[u][e] = i0 + 16 * u < n_total ? vf[u][e] : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
     l = fmaf(l, alpha, (p[0] + p[1]) + (p[2] + p[3]));
 #pragma unroll
     for (int e = 0; e < E; ++e) {

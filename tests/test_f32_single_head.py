@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+import paper_2606_02680_amd as P
 import workloads as W
 from harness import Run, compare, to_np
 
@@ -41,3 +42,25 @@ def test_f32_single_head(cuda, mode, batch, hkv, d, span, slots):
     for which in ("k", "v"):
         assert np.array_equal(run.ring_rows(rows, which),
                               run.expected_ring(rows, cfg.steps - 1, which, hist))
+
+
+@pytest.mark.parametrize("mode,d,span", [("pbb", 64, 130), ("pbb", 128, 130), ("swa", 128, 65)])
+def test_f32_infinite_value(cuda, mode, d, span):
+    """An infinite channel of the current token's value arrives as an infinity: keys past the
+    support's end, which the streams read as further copies of that token, add nothing."""
+    batch, hkv, ch = 8, 2, 9
+    g = torch.Generator().manual_seed(3)
+    kw = {"block": span} if mode == "pbb" else {"window": span}
+    desc = P.make_desc(batch, hkv, hkv, d, dtype=torch.float32, **kw)
+    fn = P.pbb_decode_step if mode == "pbb" else P.swa_decode_step
+    kr, vr = (torch.randn(batch, hkv, span, d, generator=g).to(cuda) for _ in range(2))
+    q, k, v = (torch.randn(batch, hkv, d, generator=g).to(cuda) for _ in range(3))
+    pos = torch.tensor([0, 1, 15, 16, 40, 63, 64, 777], dtype=torch.int32, device=cuda)
+    ref, out = torch.empty_like(q), torch.empty_like(q)
+    print(f"[f32 single head] infinite value {mode} {d} {span}", flush=True)
+    fn(desc, pos, q, k, v, kr, vr, ref)
+    v[..., ch] = float("inf")
+    fn(desc, pos, q, k, v, kr, vr, out)
+    assert torch.isposinf(out[..., ch]).all()
+    other = [c for c in range(d) if c != ch]
+    assert torch.equal(out[..., other], ref[..., other])
