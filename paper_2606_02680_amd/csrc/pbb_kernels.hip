@@ -1115,7 +1115,8 @@ __global__ __launch_bounds__(NW * 64) void decode_bf16_kernel(DecodeArgs a) {
       // (maximum, sum) pairs itself: every load of the merge is issued before the first is waited
       // for, so that it costs one memory round trip (staging the pairs in LDS first, and one
       // channel per load, took three and two barriers: 11.2 us per step against 9.65 at batch 4,
-      // 32/8 heads, d 128, B 2048).  States past S repeat the last one with weight 0.
+      // 32/8 heads, d 128, B 2048).  Loads past S repeat the last state, and nothing of them is
+      // added (an infinite output would give NaN with weight 0).
       const float* p0 = a.ws_part + (size_t)bg * S * G * (D + 2);
       constexpr int HD = D / 2;
       for (int i2 = tid; i2 < G * HD; i2 += NW * 64) {
@@ -1135,8 +1136,8 @@ __global__ __launch_bounds__(NW * 64) void decode_bf16_kernel(DecodeArgs a) {
         for (int sx = 0; sx < kSplitMaxWays; ++sx) {
           const float wt = sx >= S || ml[sx].x == kNegInf ? 0.0f : fast_exp2(ml[sx].x - M);
           L += wt * ml[sx].y;
-          x += wt * o[sx].x;
-          y += wt * o[sx].y;
+          x += wt * (sx < S ? o[sx].x : 0.0f);
+          y += wt * (sx < S ? o[sx].y : 0.0f);
         }
         *(uint32_t*)(out + 2 * i2) = (uint32_t)float_to_bf16_rne(x / L) |
                                      ((uint32_t)float_to_bf16_rne(y / L) << 16);

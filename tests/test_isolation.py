@@ -80,3 +80,25 @@ def test_backward_bad_log_partition(cuda, d, hq, block, window, n, t, value):
         assert not torch.isfinite(b[:, t]).all()
         for keys in (slice(0, lo), slice(t + 1, n)):
             assert torch.equal(a[:, keys], b[:, keys])
+
+
+@pytest.mark.parametrize("batch,hkv,block", [(5, 8, 2048), (2, 4, 512)])
+def test_split_decode_infinite_value(cuda, batch, hkv, block):
+    """Split launches of 6 and of 2 workgroups per unit: an infinite value of the current token
+    arrives as an infinity (the merge takes every state once, none with weight 0)."""
+    hq, d, ch = 4 * hkv, 128, 7
+    g = torch.Generator().manual_seed(9)
+    desc = P.make_desc(batch, hq, hkv, d, block=block)
+    assert P.workspace_bytes(desc) > 0
+    rings = [torch.randn(batch, hkv, block, d, generator=g).to(cuda, torch.bfloat16) for _ in range(2)]
+    q = torch.randn(batch, hq, d, generator=g).to(cuda, torch.bfloat16)
+    k, v = (torch.randn(batch, hkv, d, generator=g).to(cuda, torch.bfloat16) for _ in range(2))
+    pos = torch.arange(batch, dtype=torch.int32, device=cuda) * 37 + 3 * block + block - 200
+    ref, out = torch.empty_like(q), torch.empty_like(q)
+    print(f"[isolation] split {batch} {hkv} {block}", flush=True)
+    P.pbb_decode_step(desc, pos, q, k, v, *rings, ref)
+    v[..., ch] = float("inf")
+    P.pbb_decode_step(desc, pos, q, k, v, *rings, out)
+    assert torch.isposinf(out[..., ch]).all()
+    other = [c for c in range(d) if c != ch]
+    assert torch.equal(out[..., other], ref[..., other])
