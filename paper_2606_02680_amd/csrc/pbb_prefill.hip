@@ -150,9 +150,7 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
 
   // The wave's own range of steps [wlo, whi] (its columns' positions tw_lo .. tw_hi), and the
   // run [ua, ub) of them whose keys all lie in every column's support (a(t) never decreases).
-  // A wave with columns past the tile's positions (`cut`) masks the steps that the tile's first
-  // position does not see whole.  Zero queries, and this run of the tile alone, make what such a
-  // column adds to the wave's vote on the softmax references below independent of any query.
+  // `cut`: the wave holds columns past the tile's positions.
   const int tw_lo = t0 + pl.by_group.div(wave * 16 * QC);
   const int tw_end = t0 + pl.by_group.div(wave * 16 * QC + 16 * QC - 1);
   const bool cut = tw_end > t_last;
@@ -161,7 +159,7 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
   const int wlo = tw_lo <= t_last ? (support_lo(tw_lo) >> 5) - s_first : nsteps;
   const int whi = (tw_hi >> 5) - s_first;
   const int ua = ((a_hi + 31) >> 5) - s_first;
-  const int ub = (((cut ? t0 : tw_lo) + 1) >> 5) - s_first;
+  const int ub = ((tw_lo + 1) >> 5) - s_first;
 
   // m starts at a finite floor below any score, so that a column whose keys are all masked so
   // far gets exp2(-inf - m) = 0 without a separate test; its first real maximum always moves m.
@@ -180,13 +178,20 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
   for (int qc = 0; qc < QC; ++qc)
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(qB[qc][kk]));
+  // Columns past the tile's positions score 0 and, in masked steps, -inf: with the reference at its
+  // floor they vote for one move of the wave's references, in the tile's first step that no
+  // position masks, and with reference 0 (tiles without such a step) for none.  So what they do to
+  // the rounding of the wave's other columns depends on no query.
   if (cut) {
+    const float m0 = ua < ((t0 + 1) >> 5) - s_first ? kNoScore : 0.0f;
 #pragma unroll
-    for (int qc = 0; qc < QC; ++qc)
+    for (int qc = 0; qc < QC; ++qc) {
+      m[qc] = tcol[qc] >= 0 ? kNoScore : m0;
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk)
         qB[qc][kk] = __builtin_bit_cast(
             bf16x8, tcol[qc] >= 0 ? __builtin_bit_cast(u32x4, qB[qc][kk]) : u32x4{0u, 0u, 0u, 0u});
+    }
   }
 
   int rstage = 0;
