@@ -130,8 +130,9 @@ __device__ __forceinline__ void dma16(const unsigned char* base, uint32_t off, u
 
 // DMA of 16 rows of a tensor into half a tile, 1 KiB per instruction.  dma_offsets: this lane's
 // byte offsets from the first row (`stride` bytes between rows).  dma_rows16: the rows from the
-// wave-uniform address p, of which `left` more than the first exist (rows past them read the last
-// one instead; negative: p itself lies past it).  Callers step p along, so that a step's loads
+// wave-uniform address p, of which `left` more than the first exist (negative: p itself lies past
+// the last one); every 16-byte piece of the rows past it reads the last row's last piece, so that an
+// infinity elsewhere in that row meets no weight of 0.  Callers step p along, so that a step's loads
 // cost no multiplication: the scalar work of an issue stands in every wave's serial step (with a
 // multiplication and a limit per block, some 40 more scalar instructions per step, the d = 128
 // kernels of the backward were 2 to 3 % slower).
@@ -160,9 +161,11 @@ __device__ __forceinline__ void dma_rows16(const unsigned char* p, int left, uin
   } else {
 #pragma unroll
     for (int y = 0; y < 2 * N; ++y) {
-      const int r0 = y < N ? 0 : 8;   // first row of the block's eight, and the rows after it
-      const unsigned char* q = p + (int64_t)min(left, r0) * (int64_t)stride;
-      const uint32_t lim = (uint32_t)max(left - r0, 0) * stride + (uint32_t)(2 * D - 16);
+      const int r0 = y < N ? 0 : 8;   // first row of the block's eight
+      const bool none = left < r0;    // none of them exists
+      const unsigned char* q = p + (none ? (int64_t)left * (int64_t)stride + (2 * D - 16)
+                                         : (int64_t)r0 * (int64_t)stride);
+      const uint32_t lim = none ? 0u : (uint32_t)(left - r0) * stride + (uint32_t)(2 * D - 16);
       dma16(q, min(off[y % N], lim), lds + 1024 * y);
     }
   }

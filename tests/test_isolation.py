@@ -82,6 +82,32 @@ def test_backward_bad_log_partition(cuda, d, hq, block, window, n, t, value):
             assert torch.equal(a[:, keys], b[:, keys])
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_infinity_in_the_last_row(cuda, d):
+    """Tile rows past the prompt's end weigh 0 and must hold nothing of the last position but its
+    last 8 channels: an infinity in another channel of its value (or of its upstream gradient)
+    arrives as an infinity in its output (in dv of its support's keys), not as 0 * inf."""
+    n, hq, ch = 132, 8, 5
+    g = torch.Generator().manual_seed(8)
+    q, do = (torch.randn(2, n, hq, d, generator=g).to(cuda, torch.bfloat16) for _ in range(2))
+    k, v = (torch.randn(2, n, 2, d, generator=g).to(cuda, torch.bfloat16) for _ in range(2))
+    desc = P.make_desc(2, hq, 2, d, block=128)
+    out = torch.empty_like(q)
+    lse = torch.empty((2, hq, n), dtype=torch.float32, device=cuda)
+    v2, do2 = v.clone(), do.clone()
+    v2[:, n - 1, :, ch] = float("inf")
+    do2[:, n - 1, :, ch] = float("inf")
+    print(f"[isolation] infinity {d}", flush=True)
+    P.pbb_prefill(desc, q, k, v2, out, lse=lse)
+    assert torch.isposinf(out[:, n - 1, :, ch]).all()
+    P.pbb_prefill(desc, q, k, v, out, lse=lse)
+    dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
+    P.pbb_backward(desc, q, k, v, out, do2, lse, dq, dk, dv)
+    assert torch.isposinf(dv[:, 64:, :, ch]).all()       # the support of n - 1 is 64 .. n - 1
+    other = [c for c in range(d) if c != ch]
+    assert torch.isfinite(dv[..., other]).all()
+
+
 @pytest.mark.parametrize("batch,hkv,block", [(5, 8, 2048), (2, 4, 512)])
 def test_split_decode_infinite_value(cuda, batch, hkv, block):
     """Split launches of 6 and of 2 workgroups per unit: an infinite value of the current token
