@@ -162,11 +162,10 @@ __device__ __forceinline__ void dma_rows16(const unsigned char* p, int left, uin
 #pragma unroll
     for (int y = 0; y < 2 * N; ++y) {
       const int r0 = y < N ? 0 : 8;   // first row of the block's eight
-      const bool none = left < r0;    // none of them exists
-      const unsigned char* q = p + (none ? (int64_t)left * (int64_t)stride + (2 * D - 16)
-                                         : (int64_t)r0 * (int64_t)stride);
-      const uint32_t lim = none ? 0u : (uint32_t)(left - r0) * stride + (uint32_t)(2 * D - 16);
-      dma16(q, min(off[y % N], lim), lds + 1024 * y);
+      const int last = min(left - r0, 7);   // the last one that exists
+      const unsigned char* q = p + (int64_t)(r0 + min(last, 0)) * (int64_t)stride;
+      const uint32_t lim = (uint32_t)max(last, 0) * stride + (uint32_t)(2 * D - 16);
+      dma16(q, last < 0 ? lim : min(off[y % N], lim), lds + 1024 * y);
     }
   }
 }
