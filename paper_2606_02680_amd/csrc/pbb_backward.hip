@@ -70,6 +70,7 @@ void bwd_dq_kernel(BackwardArgs a, TilePlan pl) {
   auto support_lo = [&](int t) -> int { return pl.support_lo(t, a.block, a.window); };
   int bg, tile;
   pl.locate((int)blockIdx.x, (int)gridDim.x, bg, tile);
+  if (tile < 0) return;
   const int b = pl.by_hkv.div(bg);
   const int g = bg - b * a.hkv;
   const int t0 = tile * pl.tq;
@@ -515,11 +516,19 @@ void bwd_dkdv_kernel(BackwardArgs a, DkdvPlan pl) {
   }
 }
 
+// Where the dq launch takes the heaviest tiles first (the whole backward, by weight against in
+// order, us): 32/8 heads, d 128, B 2048, n 4000 (1000 workgroups, 3 half-blocks after the first)
+// 352 / 370, n 12000 (3000, 11) 1047 / 1028; B 512, n 8000 (2000, 31) 250 / 230.  16/1 heads, d 64,
+// B 128, n 4000 (500, 62) 47.8 / 46.9; 12/2 heads, B 2708, n 7980 (760, 5) 341 / 360.
+template <int D>
+constexpr OrderLimits kDqByWeight = {D == 128 ? 2048 : 4096, D == 128 ? 24 : 32};
+
 template <int D>
 hipError_t launch_backward_d(const BackwardArgs& a, hipStream_t stream) {
   const TilePlan pl = TilePlan::make(a.batch, a.hkv, a.group, a.n, a.mode == kSupportPBB, a.block,
-                                     16 * kDqColGroups * kDqWaves / a.group);
-  hipLaunchKernelGGL((bwd_dq_kernel<D>), dim3((unsigned)((size_t)a.batch * a.hkv * pl.tiles)),
+                                     a.window, 16 * kDqColGroups * kDqWaves / a.group,
+                                     kDqByWeight<D>);
+  hipLaunchKernelGGL((bwd_dq_kernel<D>), dim3((unsigned)((size_t)a.batch * a.hkv * pl.ranks())),
                      dim3(kDqWaves * 64), 0, stream, a, pl);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

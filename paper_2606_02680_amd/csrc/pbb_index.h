@@ -30,55 +30,80 @@ struct FastDiv {
 };
 
 // Tiles of a unit from the heaviest to the lightest.  A tile's weight is the length of its key
-// interval: with tph tiles per half-block, the tile of phase r has r + tph tile lengths of keys in
-// the half-blocks after the first, r in the first (SWA: all its tiles are one run with rising
-// weight).  So the order is: phases of half-blocks 1..J from the last phase down, then the first
-// half-block's.  The last half-block may be cut short: its `rem` phases are the lower ones.
-// (Where h is not a multiple of TQ the phases drift: still a permutation, a little off in weight.)
+// interval.  PBB: the tile that begins r tq .. (r+1) tq - 1 positions into its half-block (phase r)
+// has some r + tph tile lengths of keys in the half-blocks after the first, r in the first.  So
+// the order is: phases of half-blocks 1..J from the last phase down, then the first half-block's
+// tiles from the last down.  The last half-block may be cut short: its `rem` phases are the lower
+// ones.  Where tq does not divide the half-block, only some half-blocks have a tile of the last
+// phase; the ranks of the others are holes (tile -1).  SWA: one run with rising weight, up to the
+// first whole window, taken as a prompt within the first half-block.
 struct TileOrder {
+  int ranks;       // tiles and holes
   int first;       // tiles of the first half-block
-  int others;      // tiles after it
-  int tph, rem;    // tiles per half-block, of the last half-block
+  int others;      // ranks of the half-blocks after it
+  int rem;         // phases of the last half-block
   int cut;         // ranks of the phases that the last half-block does not have
-  FastDiv by_units, by_j, by_j1;   // units; half-blocks after the first, and all of them but one
-  static TileOrder make(int tiles, int tph, int units) {
+  int h, tq, tiles;
+  FastDiv by_tq, by_j, by_j1;   // tq; half-blocks after the first, and all of them but one
+  static TileOrder make(int n, int h, int tq) {
     TileOrder o;
-    o.tph = tph;
-    o.first = tiles < tph ? tiles : tph;
-    o.others = tiles - o.first;
-    const int j = (o.others + tph - 1) / tph;
-    o.rem = o.others - (j > 0 ? j - 1 : 0) * tph;
-    o.cut = (tph - o.rem) * (j > 0 ? j - 1 : 0);
-    o.by_units = FastDiv::make((uint32_t)units);
+    o.h = h;
+    o.tq = tq;
+    o.tiles = (n + tq - 1) / tq;
+    const int tph = (h + tq - 1) / tq;
+    const int j = (n - 1) / h;
+    o.first = o.tiles < tph ? o.tiles : tph;
+    o.rem = j > 0 ? (n - j * h + tq - 1) / tq : 0;
+    o.others = j > 0 ? (j - 1) * tph + o.rem : 0;
+    o.cut = j > 0 ? (tph - o.rem) * (j - 1) : 0;
+    o.ranks = o.first + o.others;
+    o.by_tq = FastDiv::make((uint32_t)tq);
     o.by_j = FastDiv::make((uint32_t)(j > 0 ? j : 1));
     o.by_j1 = FastDiv::make((uint32_t)(j > 1 ? j - 1 : 1));
     return o;
   }
   PBB_HD int tile(int rank) const {
     if (rank >= others) return first - 1 - (rank - others);
+    int j, r;
     if (rank < cut) {
       const int q = by_j1.div(rank);
-      return (1 + rank - q * (int)by_j1.d) * tph + tph - 1 - q;
+      j = 1 + rank - q * (int)by_j1.d;
+      r = first - 1 - q;   // (with two half-blocks after it, the first one is whole)
+    } else {
+      const int q = by_j.div(rank - cut);
+      j = 1 + rank - cut - q * (int)by_j.d;
+      r = rem - 1 - q;
     }
-    const int q = by_j.div(rank - cut);
-    return (1 + rank - cut - q * (int)by_j.d) * tph + rem - 1 - q;
+    const int t = by_tq.div(j * h + tq - 1) + r;   // the first tile of the half-block, and r more
+    return t < tiles && t * tq < (j + 1) * h ? t : -1;
   }
 };
 
-// Order of a launch's workgroups over its (unit, tile) pairs.
+// Order of a launch's workgroups over its (unit, tile) pairs: in order, or heaviest first.
 //
-// Launches of at most kByWeightMaxBlocks workgroups (16 per CU), with at least kByWeightMinPhases
-// tiles per half-block (SWA: per prompt), deal out their tiles heaviest first instead of in order.
 // In order, a CU's few workgroups often have the same phase (with 32 tiles per unit, the 32 CUs of
 // an XCD each take one tile index of every unit) and the launch waits for the CUs with the longest
-// intervals; with many workgroups per CU that evens out, and tiles in order share their keys in
-// an XCD's L2.  Measured, by weight against in order, 32/8 heads, d 128, B 2048: batch 3, n 1021
-// (768 workgroups) 36.1 against 49.1 us; batch 1, n 2000 54.8 / 58.7; batch 4, n 2048 146 / 165;
-// batch 4, n 4096 (4096) 341 / 347; batch 4, n 8192 (8192) 839 / 721.  16/4 heads, d 64, B 512 (8
-// tiles per half-block): batch 8, n 500 15.1 / 17.5, batch 4, n 8192 (4096) 81.9 / 81.5.  12/2
-// heads, d 64, B 128 (3 tiles per half-block, which mix anyway): n 16384 20.8 / 18.7.
-constexpr int kByWeightMaxBlocks = 4096;
+// intervals; with many workgroups per CU that evens out.  Heaviest first, tiles that share keys run
+// on different XCDs and further apart in time, the more so the more half-blocks a phase's tiles
+// come from.  So heaviest first is for launches whose tiles differ in weight (at least
+// kByWeightMinPhases tiles per half-block or window) with few workgroups and few half-blocks per
+// prompt.  The limits are each kernel's own (OrderLimits).  Prefill, by weight against in order, us:
+// 16/2 heads, d 128, B 2048, n 8000 (7 half-blocks after the first, 1000 workgroups) 100.3 / 123.0;
+// B 512, n 4000 (15, 500) 21.6 / 23.0, n 16000 (62, 2000) 72.2 / 64.6; 12/2 heads, d 64, B 2708,
+// n 7980 (5, 760) 65.7 / 87.7; B 338, n 42000 (248, 4000) 63.8 / 62.4.
+//
+// Sliding windows: all tiles after the first window weigh the same.  Heaviest first (that is, from
+// the last tile down) pays where the first window holds a good part of the tiles, or where it
+// spans so many tiles that walks are long: 16/4 heads, d 64, W 2048 (64 tiles): n 2400 (75 tiles
+// per unit) 40.6 / 46.9, n 16000 145.5 / 153.1; 16/2 heads, d 128, W 512 (32 tiles), n 8000 (500)
+// 45.1 / 44.6; 12/2 heads, d 64, W 128 (6 tiles), n 16384 24.2 / 22.4.
+struct OrderLimits {
+  int blocks;   // workgroups, at most
+  int halves;   // half-blocks per prompt, at most (PBB)
+};
 constexpr int kByWeightMinPhases = 8;
+constexpr int kByWeightRising = 5;       // SWA: the first window holds at least a fifth of the tiles
+constexpr int kByWeightLongWindow = 64;  // or this many
 
 // The query tiles of a prefill or dq launch: `tq` consecutive positions per tile, `tiles` per unit
 // (sequence, KV head).
@@ -86,30 +111,36 @@ struct TilePlan {
   int tq, tiles;
   int pbb;                 // 1: PBB supports, 0: sliding window
   int by_weight;           // 1: tiles are dealt out heaviest first, 0: in order
-  FastDiv by_tiles, by_hkv, by_group, by_half;
+  FastDiv by_tiles, by_units, by_hkv, by_group, by_half;
   TileOrder order;
-  static TilePlan make(int batch, int hkv, int group, int n, bool pbb, int block, int tq) {
+  static TilePlan make(int batch, int hkv, int group, int n, bool pbb, int block, int window, int tq,
+                       OrderLimits lim) {
     TilePlan p;
     p.tq = tq;
     p.tiles = (n + tq - 1) / tq;
     p.pbb = pbb;
     p.by_tiles = FastDiv::make((uint32_t)p.tiles);
+    p.by_units = FastDiv::make((uint32_t)(batch * hkv));
     p.by_hkv = FastDiv::make((uint32_t)hkv);
     p.by_group = FastDiv::make((uint32_t)group);
     p.by_half = FastDiv::make((uint32_t)(pbb ? block / 2 : 1));
-    const int tph = pbb ? block / 2 / tq : p.tiles;
-    p.by_weight = (uint64_t)batch * hkv * p.tiles <= (uint64_t)kByWeightMaxBlocks &&
-                  tph >= kByWeightMinPhases;
-    p.order = TileOrder::make(p.tiles, tph > 0 ? tph : 1, batch * hkv);
+    p.order = TileOrder::make(n, pbb ? block / 2 : n, tq);
+    const int phases = (pbb ? block / 2 : window < n ? window : n) / tq;
+    p.by_weight = (uint64_t)batch * hkv * p.tiles <= (uint64_t)lim.blocks &&
+                  phases >= kByWeightMinPhases &&
+                  (pbb ? (n - 1) / (block / 2) < lim.halves
+                       : phases >= kByWeightLongWindow || p.tiles <= kByWeightRising * phases);
     return p;
   }
-  // Unit and tile of workgroup k of `blocks`.  Workgroup k runs on XCD k mod 8: in order, each XCD
-  // takes a contiguous run of tiles, so that tiles sharing keys (neighbours of one unit) share
-  // that XCD's L2.
+  // Workgroups per unit.
+  int ranks() const { return by_weight ? order.ranks : tiles; }
+  // Unit and tile of workgroup k of `blocks` (tile -1: none).  Workgroup k runs on XCD k mod 8: in
+  // order, each XCD takes a contiguous run of tiles, so that tiles sharing keys (neighbours of one
+  // unit) share that XCD's L2.
   PBB_HD void locate(int k, int blocks, int& unit, int& tile) const {
     if (by_weight) {
-      const int rank = order.by_units.div(k);
-      unit = k - rank * (int)order.by_units.d;
+      const int rank = by_units.div(k);
+      unit = k - rank * (int)by_units.d;
       tile = order.tile(rank);
     } else {
       const int per = blocks >> 3, rem = blocks & 7;
