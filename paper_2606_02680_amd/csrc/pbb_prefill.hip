@@ -29,9 +29,12 @@
 // instead of divisions, packed conversions and 16-byte stores in the epilogue, steps skipped per
 // wave, scalar-stepped tile addresses and LDS addresses that are two or four lane constants plus
 // immediates took the paper's shape (12/2 heads, d 64, B 128, n 65536; 238 MB) from 74.1 to 61.4
-// us (3.9 TB/s) and c3's heads (n 16384, batch 4) from 1529 to 1485 us (1065 TFLOP/s).  32x32x16 matrix instructions in the
-// same structure (32 columns at once, a fifth fewer vector instructions) measured 1574 us there
-// and 62.0 at the paper's shape.
+// us (3.9 TB/s) and c3's heads (n 16384, batch 4) from 1529 to 1485 us (1065 TFLOP/s), loops of
+// their own for masked and unmasked steps another 1 to 2 % there.  32x32x16 matrix instructions
+// (32 columns at once, a fifth fewer vector instructions) measured 1574 against 1485 us and 62.0
+// against 61.4.
+
+#include <type_traits>
 
 #include "pbb_device.h"
 #include "pbb_internal.h"
@@ -46,9 +49,9 @@ constexpr int kPrefillWaves = 4;
 constexpr int kPrefillGroups = 2;
 constexpr int kPrefillCols = 16 * kPrefillGroups * kPrefillWaves;
 // LDS stages and the occupancy the register budget is set for (waves per SIMD = workgroups per
-// CU): three at d = 128 (166 VGPRs, 48 KiB of LDS), four at d = 64 (106 VGPRs, 32 KiB).  Deeper
-// pipelines cost occupancy: five and eight stages are 20 to 60 % slower, at one workgroup per CU
-// too.
+// CU): three at d = 128 (168 VGPRs and 12 bytes of scratch that the last masked steps use, 48 KiB of
+// LDS), four at d = 64 (128 VGPRs, 32 KiB).  Five stages at d = 64 (three workgroups per CU) take 9.2
+// against 7.8 us at 12/2 heads, B 128, n 2048, 56.5 / 55.4 at n 65536, and the same at large blocks.
 constexpr int kPrefillStages128 = 3, kPrefillOcc128 = 3;
 constexpr int kPrefillStages64 = 4, kPrefillOcc64 = 4;
 // Starting reference of the running maximum (log2 units): finite and below any score.
@@ -198,7 +201,8 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
   int rstage = 0;
   constexpr int OPS = D / 32;           // DMA instructions of a wave per step
 
-  for (int st = 0; st < nsteps; ++st) {
+  // Begins step st: its tiles have landed; returns the stage offset.
+  auto begin_step = [&](int st) -> uint32_t {
     // This wave's loads of step st have landed once at most the loads of the steps issued
     // after it (up to STAGES - 2) are outstanding; the barrier then covers every wave's loads,
     // and every wave is done with step st-1, whose stage the loads of step st+STAGES-1 reuse.
@@ -209,8 +213,13 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
     __builtin_amdgcn_sched_barrier(0);
     const uint32_t sb = (uint32_t)(rstage * BUF);
     rstage = rstage == STAGES - 1 ? 0 : rstage + 1;
-    if (st < wlo || st > whi) continue;
+    return sb;
+  };
 
+  // One step, masked or not: each its own loop below (a branch around the mask inside one loop cost
+  // 2 to 6 %: 8/8 heads, d 128, B 2048, n 2048 51.6 -> 48.6 us, 32/8 heads, batch 4, n 8192 709 ->
+  // 697; 16/4 heads, d 64, W 2048, n 32000 293 -> 280).
+  auto step = [&](int st, uint32_t sb, auto masked) {
     f32x4 s0[QC], s1[QC];
 #pragma unroll
     for (int qc = 0; qc < QC; ++qc) {
@@ -229,7 +238,7 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
       }
     }
     // Element e of s0 is key k0 + 4 j4 + e of the lane's column, of s1 key k0 + 16 + 4 j4 + e.
-    if (st < ua || st >= ub) {
+    if constexpr (decltype(masked)::value) {
       const int k0 = (s_first + st) * 32 + 4 * j4;
 #pragma unroll
       for (int qc = 0; qc < QC; ++qc) {
@@ -280,7 +289,21 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
 #pragma unroll
       for (int qc = 0; qc < QC; ++qc) m[qc] = fmaxf(m[qc], column_max(qc));
     }
-    if (__builtin_amdgcn_ballot_w64(weights()) != 0) {
+    // V^T operand of O^T += V^T P^T: lane (c16, j4) needs channel 16nb + c16 of keys
+    // 4j4..4j4+3 and 16+4j4..16+4j4+3 (the key order of P^T in the score layout).  One
+    // transposed read per half: within each 16-lane group, lane i names 4 channels
+    // 16nb + 4(i mod 4) .. +3 of key row 4j4 + i/4, and lane c16 receives channel 16nb + c16 of
+    // those four rows.  At d = 64 the reads travel under the weights, which hides them where few
+    // waves share a SIMD (12/2 heads, B 2048, n 2048, 98 workgroups per unit: 40.6 -> 37.3 us; at
+    // the paper's shape 53.7 -> 53.2); at d = 128 their 32 registers would be spilled.
+    u32x2 vr[2 * NB];
+    if constexpr (D == 64) {
+      read_chunks<D, TILE>(vr, va, sb);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const bool over = weights();
+    if constexpr (D == 64) wait_chunks<D>(vr);
+    if (__builtin_amdgcn_ballot_w64(over) != 0) {
 #pragma unroll
       for (int qc = 0; qc < QC; ++qc) {
         const float cand = column_max(qc);
@@ -295,14 +318,10 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
     }
 #pragma unroll
     for (int qc = 0; qc < QC; ++qc) lsum[qc] += ps[qc];
-    // V^T operand of O^T += V^T P^T: lane (c16, j4) needs channel 16nb + c16 of keys
-    // 4j4..4j4+3 and 16+4j4..16+4j4+3 (the key order of P^T in the score layout).  One
-    // transposed read per half: within each 16-lane group, lane i names 4 channels
-    // 16nb + 4(i mod 4) .. +3 of key row 4j4 + i/4, and lane c16 receives channel 16nb + c16 of
-    // those four rows.
-    u32x2 vr[2 * NB];
-    read_chunks<D, TILE>(vr, va, sb);
-    wait_chunks<D>(vr);
+    if constexpr (D == 128) {
+      read_chunks<D, TILE>(vr, va, sb);
+      wait_chunks<D>(vr);
+    }
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       const bf16x8 vt = join_chunks(vr[2 * nb], vr[2 * nb + 1]);
@@ -311,7 +330,25 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
         acc[qc][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt, pB[qc], acc[qc][nb], 0, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
+  };
+
+  const int m1 = min(max(ua, wlo), whi + 1);   // [m1, m2): no masks
+  const int m2 = min(max(ub, m1), whi + 1);
+  int st = 0;
+  for (; st < wlo; ++st) begin_step(st);
+  for (; st < m1; ++st) {
+    const uint32_t sb = begin_step(st);
+    step(st, sb, std::true_type{});
   }
+  for (; st < m2; ++st) {
+    const uint32_t sb = begin_step(st);
+    step(st, sb, std::false_type{});
+  }
+  for (; st <= whi; ++st) {
+    const uint32_t sb = begin_step(st);
+    step(st, sb, std::true_type{});
+  }
+  for (; st < nsteps; ++st) begin_step(st);
 
   // Outputs: o = acc / l (bf16 RNE), lse = (m + log2 l) * ln 2.  Lane (c16, j4) holds channels
   // 16nb + 4j4 .. +3 of its column; a swap of neighbouring quarters gives each lane 8 consecutive
