@@ -396,10 +396,11 @@ void bwd_dkdv_kernel(BackwardArgs a, DkdvPlan pl) {
     // the dout.v products land on -delta of their target row.
     f32x4 s0 = {0.0f, 0.0f, 0.0f, 0.0f}, s1 = {0.0f, 0.0f, 0.0f, 0.0f};
     // The Q rows first; the dout rows travel under the score products, whose exponentials then run
-    // beside the dout.v products.  At d = 128 the order is pinned (two waves per SIMD do not hide
-    // the waits that the scheduler spreads between the products: 3469 against 3585 us at c3's
-    // heads; the dout^T reads pinned before the dout.v products as well 3814 us); at d = 64 four
-    // waves do, and its order is the faster one (64 against 68 us at the paper's shape).
+    // beside the dout.v products.  The order is pinned: few waves per SIMD do not hide the waits that
+    // the scheduler spreads between the products (3469 against 3585 us at c3's heads; the dout^T
+    // reads pinned before the dout.v products as well 3814 us; the whole backward at d = 64, 12/2
+    // heads, B 2048, n 2048 217.7 / 229.3, 16/1 heads, n 2000 503.9 / 531.3; with four waves per SIMD
+    // no difference: the paper's shape 158.0 / 157.4).
     bf16x8 qa[KK], qb[KK], ga[KK], gb[KK];
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
@@ -407,10 +408,8 @@ void bwd_dkdv_kernel(BackwardArgs a, DkdvPlan pl) {
       qa[kk] = *(lds_row)(p);
       qb[kk] = *(lds_row)(p + HALF);
     }
-    if constexpr (D == 128) {
-      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
     f32x4 d0 = *(lds_f4)(lds0 + la + sb + 128), d1 = *(lds_f4)(lds0 + la + sb + 192);
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
@@ -424,7 +423,7 @@ void bwd_dkdv_kernel(BackwardArgs a, DkdvPlan pl) {
       s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[kk], kB[kk], s0, 0, 0, 0);
       s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qb[kk], kB[kk], s1, 0, 0, 0);
     }
-    if constexpr (D == 128) __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
       d0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ga[kk], vB[kk], d0, 0, 0, 0);
