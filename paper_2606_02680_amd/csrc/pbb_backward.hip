@@ -185,15 +185,18 @@ void bwd_dq_kernel(BackwardArgs a, TilePlan pl) {
   const float c = a.scale_log2;
   int rstage = 0;
 
-  for (int st = 0; st < nsteps; ++st) {
+  auto begin_step = [&](int st) -> uint32_t {
     wait_groups<STAGES - 2, OPS>(nsteps - 1 - st);
     lds_barrier();
     if (st + STAGES - 1 < nsteps) issue(rstage == 0 ? STAGES - 1 : rstage - 1);
     __builtin_amdgcn_sched_barrier(0);
     const uint32_t sb = (uint32_t)(rstage * BUF);
     rstage = rstage == STAGES - 1 ? 0 : rstage + 1;
-    if (st < wlo || st > whi) continue;
+    return sb;
+  };
 
+  // One step, masked or not: each its own loop below.
+  auto step = [&](int st, uint32_t sb, auto masked) {
     f32x4 s0[QC], s1[QC], d0[QC], d1[QC];
 #pragma unroll
     for (int qc = 0; qc < QC; ++qc) {
@@ -220,29 +223,23 @@ void bwd_dq_kernel(BackwardArgs a, TilePlan pl) {
     // The K^T reads for dq go out now, under the softmax arithmetic.
     u32x2 kr[2 * NB];
     read_chunks<D, 0>(kr, ka, sb);
-    // Masked keys score -inf and get p = 0.  Element e of s0 is key k0 + 4 j4 + e, of s1 key
-    // k0 + 16 + 4 j4 + e.
-    if (st < ua || st >= ub) {
-      const int k0 = (s_first + st) * 32 + 4 * j4;
-#pragma unroll
-      for (int qc = 0; qc < QC; ++qc) {
-        const int lo = lo_c[qc] - k0, up = tcol[qc] - k0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          s0[qc][e] = e >= lo && e <= up ? s0[qc][e] : kNegInf;
-          s1[qc][e] = 16 + e >= lo && 16 + e <= up ? s1[qc][e] : kNegInf;
-        }
-      }
-    }
-    // ds = p (dp - delta) (the accumulators started at -delta), p = exp2(s c - lse2).
+    // ds = p (dp - delta) (the accumulators started at -delta), p = exp2(s c - lse2).  Masked keys
+    // get p = 0 whatever the target's log-partition is (their exponent is replaced).  Element e of
+    // s0 is key k0 + 4 j4 + e, of s1 key k0 + 16 + 4 j4 + e.
+    const int k0 = (s_first + st) * 32 + 4 * j4;
     bf16x8 dsB[QC];
 #pragma unroll
     for (int qc = 0; qc < QC; ++qc) {
+      const int lo = lo_c[qc] - k0, up = tcol[qc] - k0;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float sc = e < 4 ? s0[qc][e] : s1[qc][e - 4];
         const float dp = e < 4 ? d0[qc][e] : d1[qc][e - 4];
-        dsB[qc][e] = (__bf16)(fast_exp2(__builtin_fmaf(sc, c, -lse2[qc])) * dp);
+        float x = __builtin_fmaf(e < 4 ? s0[qc][e] : s1[qc][e - 4], c, -lse2[qc]);
+        if constexpr (decltype(masked)::value) {
+          const int t = e < 4 ? e : 12 + e;
+          x = t >= lo && t <= up ? x : kNegInf;
+        }
+        dsB[qc][e] = (__bf16)(fast_exp2(x) * dp);
       }
     }
     // dq^T += K^T ds^T.
@@ -255,7 +252,25 @@ void bwd_dq_kernel(BackwardArgs a, TilePlan pl) {
         acc[qc][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt, dsB[qc], acc[qc][nb], 0, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
+  };
+
+  const int m1 = min(max(ua, wlo), whi + 1);   // [m1, m2): no masks
+  const int m2 = min(max(ub, m1), whi + 1);
+  int st = 0;
+  for (; st < wlo; ++st) begin_step(st);
+  for (; st < m1; ++st) {
+    const uint32_t sb = begin_step(st);
+    step(st, sb, std::true_type{});
   }
+  for (; st < m2; ++st) {
+    const uint32_t sb = begin_step(st);
+    step(st, sb, std::false_type{});
+  }
+  for (; st <= whi; ++st) {
+    const uint32_t sb = begin_step(st);
+    step(st, sb, std::true_type{});
+  }
+  for (; st < nsteps; ++st) begin_step(st);
 
   // (The columns are worked out again: kept across the key loop, they would cost registers.)
   int ce = c16;

@@ -83,6 +83,25 @@ def test_backward_bad_log_partition(cuda, d, hq, block, window, n, t, value):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+def test_backward_infinite_weight(cuda, d):
+    """The first position sees only itself: with a log-partition of -inf its weight is infinite, and
+    so is its dq (keys outside the support weigh exactly 0, not exp(-inf + inf))."""
+    n, hq = 40, 4
+    g = torch.Generator().manual_seed(7)
+    q, do = (torch.randn(2, n, hq, d, generator=g).to(cuda, torch.bfloat16) for _ in range(2))
+    k, v = (torch.randn(2, n, 2, d, generator=g).to(cuda, torch.bfloat16) for _ in range(2))
+    desc = P.make_desc(2, hq, 2, d, block=64)
+    out = torch.zeros_like(q)
+    lse = torch.zeros((2, hq, n), dtype=torch.float32, device=cuda)
+    lse[:, :, 0] = float("-inf")
+    dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
+    print(f"[isolation] infinite weight {d}", flush=True)
+    P.pbb_backward(desc, q, k, v, out, do, lse, dq, dk, dv)
+    assert torch.isinf(dq[:, 0]).all()
+    assert torch.isfinite(dq[:, 1:]).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
 def test_infinity_in_the_last_row(cuda, d):
     """Tile rows past the prompt's end weigh 0 and must hold nothing of the last position but its
     last 8 channels: an infinity in another channel of its value (or of its upstream gradient)
