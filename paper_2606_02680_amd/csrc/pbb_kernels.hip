@@ -1280,14 +1280,20 @@ void launch_f32(const DecodeArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_decode_f32(const DecodeArgs& a, int32_t head_dim, hipStream_t stream) {
-  // Non-temporal loads by the rule of the bf16 launches (8 bytes per element of the two rings).
-  // Measured with and without, in one process: batch 512, 16/2 heads, B 1024 (1 GiB of rings)
-  // 151 against 162 us per step, 32/8 heads, batch 256, B 2048 515 against 559 us, G = 1 as above
-  // 507 against 551 us.  (K's loads take 64 bytes of a row per instruction; temporal loads for K
-  // alone are 2 % faster at the second shape when its rings repeat, and 19 % slower at the first
-  // on rings not read before.)
-  const double ring_bytes = 8.0 * (double)(a.batch * a.hkv) * (double)a.slots * (double)head_dim;
-  const bool nt = ring_bytes > kStreamBytes;
+  // Non-temporal loads (8 bytes per element of the two rings).  One query head: by the rule of the
+  // bf16 launches (batch 64, 8 heads, d 128, B 2048 138 against 155 us per step, batch 8, B 8192 172
+  // / 186).  Matrix cores: not with fewer workgroups than CUs, whose latency they add to (32/8 heads,
+  // d 128, W 4096: batch 16 141 / 122 us, batch 24 158 / 147, batch 32 173 / 188; batch 256, B 2048
+  // 515 / 559), up to 1.5 times the cache, part of which a repeated step finds in it (16/2 heads,
+  // batch 192, B 1024 76.5 / 69.5, on rings not read before 75.7 / 75.9; batch 512 154 / 159), and
+  // not with many short walks at d = 128 (16/2 heads, batch 2048, B 256 200 / 187, but batch 1024,
+  // B 1024 280 / 295; 16/1 heads, batch 2048, B 512 183 / 173).
+  const int64_t units = (int64_t)a.batch * a.hkv;
+  const double ring_bytes = 8.0 * (double)units * (double)a.slots * (double)head_dim;
+  const bool many_short = head_dim == 128 && a.slots <= 512 && units * a.group >= 16384;
+  const bool nt = a.group < kF32MatrixMinGroup
+                      ? ring_bytes > kStreamBytes
+                      : ring_bytes > 1.5 * kStreamBytes && units >= 256 && !many_short;
   if (head_dim == 128) {
     if (nt) launch_f32<128, true>(a, stream);
     else launch_f32<128, false>(a, stream);
