@@ -224,7 +224,7 @@ pbb_status_t backward_common(const pbb_desc_t* desc, bool swa, int32_t n, const 
     return PBB_ERR_SHAPE;
   // 32 rows of one tensor lie within 32-bit byte offsets of the first
   if ((uint64_t)desc->n_q_heads * (uint64_t)desc->head_dim > (1u << 24)) return PBB_ERR_SHAPE;
-  // the delta launch covers 16 (d = 128) or 32 rows of batch x n x Hq per workgroup
+  // at most 2^35 query rows (4 TiB of queries at d = 64)
   if ((uint64_t)desc->batch * (uint64_t)desc->n_q_heads * (uint64_t)n / 16 + 1 > 0x7fffffffull)
     return PBB_ERR_SHAPE;
   if (n == 0) return PBB_OK;

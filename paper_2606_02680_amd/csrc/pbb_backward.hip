@@ -22,12 +22,13 @@
 // the forward (16 B-operand columns, 32 rows in two halves), P and dS rounded to bf16 as
 // operands, fp32 accumulation, bf16 (RNE) outputs.
 //
-// Bound.  Paper's shape (12/2 heads, d 64, B 128, n 65536): dq moves 437 MB in 93 us (4.7 TB/s,
-// near a copy's rate), dk/dv 267 MB in 64 us; FastDiv index arithmetic, 16-byte stores, steps
+// Bound.  Paper's shape (12/2 heads, d 64, B 128, n 65536): dq moves 446 MB in 94 us (4.7 TB/s,
+// near a copy's rate), dk/dv 275 MB in 66 us; FastDiv index arithmetic, 16-byte stores, steps
 // skipped per wave and scalar-stepped tile addresses took them from 105 and 72 us.  c3's heads
-// (n 16384, batch 4): 2.24 and 3.47 ms (1060 and 910 TFLOP/s), bound by each wave's serial step at
-// two waves per SIMD while the card's power limit holds the clock near 1.9 GHz: dropping the
-// transposed reads or the exponentials from a copy of the kernel changed its time by 1 to 3 %.
+// (n 16384, batch 4): 2.07 and 3.32 ms (1150 and 950 TFLOP/s of the 6 d and 8 d operations per pair
+// that each computes), bound by each wave's serial step at two waves per SIMD (matrix cores busy
+// 0.57 and 0.48) while the card's power limit holds the clock near 2.0 GHz: dropping the transposed
+// reads or the exponentials from a copy of the kernel changed its time by 1 to 3 %.
 // 32x32x16 products measured 5 % slower for dq there, and for dk/dv (32 keys per wave) 96 against
 // 72 us at d = 64 and twice as slow at d = 128 (one wave per SIMD, accumulators copied between
 // register files every step).

@@ -123,10 +123,10 @@ hipError_t launch_decode_bf16(const DecodeArgs& a, int32_t head_dim, hipStream_t
 // bf16 prefill on matrix cores; head_dim 64 or 128; n >= 1.
 hipError_t launch_prefill_bf16(const PrefillArgs& a, int32_t head_dim, hipStream_t stream);
 
-// bf16 backward on matrix cores: delta, then dq, then dk/dv; head_dim 64 or 128; n >= 1.
+// bf16 backward on matrix cores: dq (with delta), then dk/dv; head_dim 64 or 128; n >= 1.
 hipError_t launch_backward_bf16(const BackwardArgs& a, int32_t head_dim, hipStream_t stream);
 
-// fp32 decode on vector ALUs; head_dim 64 or 128.
+// fp32 decode, on matrix cores (one query head per KV head: on vector ALUs); head_dim 64 or 128.
 hipError_t launch_decode_f32(const DecodeArgs& a, int32_t head_dim, hipStream_t stream);
 
 // The library-held decode workspace of the current device (kNoAllocScratchBytes bytes): its

@@ -215,7 +215,7 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(DecodeArgs a) {
 #pragma unroll
     for (int u = 0; u < U; ++u) p[u] = fast_exp2(s[u] - mn);
     // Masked keys add nothing, also where v_new is infinite (0 * inf).  Only a stream's last keys
-    // can be masked: selects in every iteration cost registers (101 against 78 at d = 128) and 18.2
+    // can be masked: selects in every iteration cost registers (101 against 92 at d = 128) and 18.2
     // us where this branch takes 15.5 (one sequence, 8 heads, d 128, B 2048).
     if (i0 + 16 * (U - 1) >= n_total) {
 #pragma unroll
