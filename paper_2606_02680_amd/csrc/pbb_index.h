@@ -94,14 +94,19 @@ struct TileOrder {
 //
 // Sliding windows: all tiles after the first window weigh the same.  Heaviest first (that is, from
 // the last tile down) pays where the first window holds a good part of the tiles, or where it
-// spans so many tiles that walks are long: 16/4 heads, d 64, W 2048 (64 tiles): n 2400 (75 tiles
-// per unit) 40.6 / 46.9, n 16000 145.5 / 153.1; 16/2 heads, d 128, W 512 (32 tiles), n 8000 (500)
-// 45.1 / 44.6; 12/2 heads, d 64, W 128 (6 tiles), n 16384 24.2 / 22.4.
-struct OrderLimits {
+// spans so many tiles that walks are long: 16/4 heads, d 64, W 2048 (64 tiles), n 16000 (500 tiles
+// per unit) 145.5 / 153.1; 16/2 heads, d 128, W 512 (32 tiles), n 8000 (500) 45.1 / 44.6; 12/2
+// heads, d 64, W 128 (6 tiles), n 16384 24.2 / 22.4.  With one to two workgroups per CU it pays where
+// the second ones are all of the first window: 12/2 heads, d 64, 300 workgroups: W 672 (64 of them
+// light) 15 % faster, W 336 (32) 2 %; 500 workgroups: W 1344 (128) 0.5 % slower.
+struct OrderLimits {   // (PBB)
   int blocks;   // workgroups, at most
-  int halves;   // half-blocks per prompt, at most (PBB)
+  int halves;   // half-blocks per prompt, at most
 };
 constexpr int kByWeightMinPhases = 8;
+constexpr int kByWeightMinWindow = 4;    // SWA (batch 8, 16/4 heads, d 64, W 240, n 708: 13.4 / 14.8)
+constexpr int kByWeightMaxWindow = 4096; // SWA: workgroups, at most
+constexpr int kCUs = 256;
 constexpr int kByWeightRising = 5;       // SWA: the first window holds at least a fifth of the tiles
 constexpr int kByWeightLongWindow = 64;  // or this many
 
@@ -126,10 +131,16 @@ struct TilePlan {
     p.by_half = FastDiv::make((uint32_t)(pbb ? block / 2 : 1));
     p.order = TileOrder::make(n, pbb ? block / 2 : n, tq);
     const int phases = (pbb ? block / 2 : window < n ? window : n) / tq;
-    p.by_weight = (uint64_t)batch * hkv * p.tiles <= (uint64_t)lim.blocks &&
-                  phases >= kByWeightMinPhases &&
-                  (pbb ? (n - 1) / (block / 2) < lim.halves
-                       : phases >= kByWeightLongWindow || p.tiles <= kByWeightRising * phases);
+    const int64_t units = (int64_t)batch * hkv, blocks = units * p.tiles;
+    bool pays;
+    if (pbb)
+      pays = phases >= kByWeightMinPhases && (n - 1) / (block / 2) < lim.halves;
+    else if (blocks <= 2 * kCUs)
+      pays = phases >= kByWeightMinWindow && units * phases >= blocks - kCUs;
+    else
+      pays = phases >= kByWeightLongWindow ||
+             (phases >= kByWeightMinWindow && p.tiles <= kByWeightRising * phases);
+    p.by_weight = pays && blocks <= (pbb ? lim.blocks : kByWeightMaxWindow);
     return p;
   }
   // Workgroups per unit.

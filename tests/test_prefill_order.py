@@ -43,7 +43,7 @@ int main() {
     const int n = 1 + rng() % (i % 2 ? 40000 : 3000);
     const int block = 2 * (1 + rng() % (i % 3 ? 2500 : 200)), window = 1 + rng() % 5000;
     const bool pbb = i % 4 != 0;
-    const pbb::OrderLimits lim = {i % 5 ? 1 << 30 : 0, 1 << 30};
+    const pbb::OrderLimits lim = {i % 5 ? 1 << 30 : 0, 1 << 30};   // (PBB: both orders)
     const auto p = pbb::TilePlan::make(batch, hkv, group, n, pbb, block, window, tq, lim);
     const int units = batch * hkv, blocks = units * p.ranks();
     std::vector<char> seen((size_t)units * p.tiles, 0);
