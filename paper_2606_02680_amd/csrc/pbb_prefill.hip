@@ -30,7 +30,7 @@
 // wave, scalar-stepped tile addresses and LDS addresses that are two or four lane constants plus
 // immediates took the paper's shape (12/2 heads, d 64, B 128, n 65536; 238 MB) from 74.1 to 61.4
 // us (3.9 TB/s) and c3's heads (n 16384, batch 4) from 1529 to 1485 us (1065 TFLOP/s), loops of
-// their own for masked and unmasked steps another 1 to 2 % there.  32x32x16 matrix instructions
+// their own for masked and unmasked steps (long walks only) another 1 to 2 % there.  32x32x16 matrix instructions
 // (32 columns at once, a fifth fewer vector instructions) measured 1574 against 1485 us and 62.0
 // against 61.4.
 
@@ -49,15 +49,16 @@ constexpr int kPrefillWaves = 4;
 constexpr int kPrefillGroups = 2;
 constexpr int kPrefillCols = 16 * kPrefillGroups * kPrefillWaves;
 // LDS stages and the occupancy the register budget is set for (waves per SIMD = workgroups per
-// CU): three at d = 128 (168 VGPRs and 12 bytes of scratch that the last masked steps use, 48 KiB of
-// LDS), four at d = 64 (128 VGPRs, 32 KiB).  Five stages at d = 64 (three workgroups per CU) take 9.2
+// CU): three at d = 128 (168 VGPRs and, with loops apart, 12 bytes of scratch that the last masked
+// steps use, 48 KiB of LDS), four at d = 64 (128 VGPRs, 32 KiB).  Five stages at d = 64 (three workgroups per CU) take 9.2
 // against 7.8 us at 12/2 heads, B 128, n 2048, 56.5 / 55.4 at n 65536, and the same at large blocks.
 constexpr int kPrefillStages128 = 3, kPrefillOcc128 = 3;
 constexpr int kPrefillStages64 = 4, kPrefillOcc64 = 4;
 // Starting reference of the running maximum (log2 units): finite and below any score.
 constexpr float kNoScore = -1.0e30f;
 
-template <int D, int ST, int OCC>
+// LOOPS: masked and unmasked steps in loops of their own (kPrefillLoopKeys).
+template <int D, int ST, int OCC, bool LOOPS>
 __global__ __launch_bounds__(kPrefillWaves * 64) __attribute__((amdgpu_waves_per_eu(OCC)))
 void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
   constexpr int NW = kPrefillWaves;
@@ -216,9 +217,7 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
     return sb;
   };
 
-  // One step, masked or not: each its own loop below (a branch around the mask inside one loop cost
-  // 2 to 6 %: 8/8 heads, d 128, B 2048, n 2048 51.6 -> 48.6 us, 32/8 heads, batch 4, n 8192 709 ->
-  // 697; 16/4 heads, d 64, W 2048, n 32000 293 -> 280).
+  // One step, masked or not: with LOOPS by the loop that it stands in, else by a branch.
   auto step = [&](int st, uint32_t sb, auto masked) {
     f32x4 s0[QC], s1[QC];
 #pragma unroll
@@ -238,7 +237,7 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
       }
     }
     // Element e of s0 is key k0 + 4 j4 + e of the lane's column, of s1 key k0 + 16 + 4 j4 + e.
-    if constexpr (decltype(masked)::value) {
+    if (LOOPS ? decltype(masked)::value : st < ua || st >= ub) {
       const int k0 = (s_first + st) * 32 + 4 * j4;
 #pragma unroll
       for (int qc = 0; qc < QC; ++qc) {
@@ -336,13 +335,15 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
   const int m2 = min(max(ub, m1), whi + 1);
   int st = 0;
   for (; st < wlo; ++st) begin_step(st);
-  for (; st < m1; ++st) {
-    const uint32_t sb = begin_step(st);
-    step(st, sb, std::true_type{});
-  }
-  for (; st < m2; ++st) {
-    const uint32_t sb = begin_step(st);
-    step(st, sb, std::false_type{});
+  if constexpr (LOOPS) {
+    for (; st < m1; ++st) {
+      const uint32_t sb = begin_step(st);
+      step(st, sb, std::true_type{});
+    }
+    for (; st < m2; ++st) {
+      const uint32_t sb = begin_step(st);
+      step(st, sb, std::false_type{});
+    }
   }
   for (; st <= whi; ++st) {
     const uint32_t sb = begin_step(st);
@@ -399,13 +400,21 @@ void prefill_bf16_kernel(PrefillArgs a, TilePlan pl) {
 template <int D>
 constexpr OrderLimits kPrefillByWeight = {4096, D == 128 ? 24 : 96};
 
-template <int D, int ST, int OCC>
-hipError_t launch_prefill_d(const PrefillArgs& a, hipStream_t stream) {
+// Keys of a half-block (or window) from which masked and unmasked steps stand in loops of their own
+// at d = 128 (always at d = 64).  A branch around the mask inside one loop lengthens every step, loops
+// apart take 12 bytes of scratch and more instructions to fetch, which counts in short walks.  Apart
+// against together, us: 8/8 heads, B 4096, n 16384 181.4 / 190.7; 32/8 heads, B 2048, batch 4, n 16384
+// 1450 / 1467; 24/8 heads, W 2578, batch 4, n 2829 180 / 185; 8/8 heads, W 903, n 58082 262.5 / 262.0;
+// 32/8 heads, B 1024, batch 2, n 8192 237.7 / 234.6; 24/8 heads, B 78, batch 7, n 14977 376 / 360.
+constexpr int kPrefillLoopKeys = 1024;
+
+template <int D, int ST, int OCC, bool LOOPS>
+hipError_t launch_prefill_loops(const PrefillArgs& a, hipStream_t stream) {
   const TilePlan pl = TilePlan::make(a.batch, a.hkv, a.group, a.n, a.mode == kSupportPBB, a.block,
                                      a.window, kPrefillCols / a.group, kPrefillByWeight<D>);
   const size_t blocks = (size_t)a.batch * a.hkv * pl.ranks();
   if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((prefill_bf16_kernel<D, ST, OCC>), dim3((unsigned)blocks),
+  hipLaunchKernelGGL((prefill_bf16_kernel<D, ST, OCC, LOOPS>), dim3((unsigned)blocks),
                      dim3(kPrefillWaves * 64), 0, stream, a, pl);
   return hipGetLastError();
 }
@@ -413,8 +422,12 @@ hipError_t launch_prefill_d(const PrefillArgs& a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_prefill_bf16(const PrefillArgs& a, int32_t head_dim, hipStream_t stream) {
-  return head_dim == 128 ? launch_prefill_d<128, kPrefillStages128, kPrefillOcc128>(a, stream)
-                         : launch_prefill_d<64, kPrefillStages64, kPrefillOcc64>(a, stream);
+  if (head_dim == 64)
+    return launch_prefill_loops<64, kPrefillStages64, kPrefillOcc64, true>(a, stream);
+  const int keys = a.mode == kSupportPBB ? a.block / 2 : a.window;
+  return (keys < a.n ? keys : a.n) >= kPrefillLoopKeys
+             ? launch_prefill_loops<128, kPrefillStages128, kPrefillOcc128, true>(a, stream)
+             : launch_prefill_loops<128, kPrefillStages128, kPrefillOcc128, false>(a, stream);
 }
 
 }  // namespace pbb
